@@ -103,7 +103,8 @@ namespace wd {
 // The three low-precision block buffers (FP32-sized), allocated on first use;
 // a buffer whose allocation failed earlier is tried again.
 int lowp_ensure(wd_ctx* c) {
-    const size_t bytes = block_elems(c, c->max_L) * sizeof(float2);
+    if (!lowp_ok(c->g)) return WD_ENOMEM;
+    const size_t bytes = lowp_tiles(c->g) * 768 * c->max_L * sizeof(float2);
     for (int i = 0; i < 3; ++i) {
         if (c->lp[i]) continue;
         int r = dev_alloc(&c->lp[i], bytes);
@@ -226,7 +227,7 @@ int wd_set_links(wd_ctx* c, const double* U, int on_device) {
         src = (const double2*)staging;
     }
     hipError_t e = launch_links_from_abi(src, c->f.U, c->g, c->bc_t, c->stream);
-    if (e == hipSuccess) e = launch_convert(c->f.U, c->U32, Prec::F32, 1.0, n, c->stream);
+    if (e == hipSuccess) e = launch_links_f32(c->f.U, c->U32, c->g.V, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (staging && staging != c->ws[WS_T2]) dev_free(staging);
     if (e != hipSuccess) return WD_EHIP;

@@ -175,16 +175,16 @@ __device__ __forceinline__ void third_row(cx<R> (&u)[9], R invk, bool neg) {
 // once and applied to every column.  Xc is the wave-uniform base of the
 // thread's first column; link_off and nb_off are byte offsets of the link's
 // site and of the neighbour site inside one plane; V is the number of sites
-// (the plane stride of the links and 12 V the column stride of the block
-// vector), KS the block vector's plane stride.  LT: the links may be tiled
+// (the plane stride of the links), cs and KS the block vector's column and
+// plane strides.  LT: the links may be tiled
 // (FP64 fields), with their plane stride in LS (V, or 64 when tiled).  SC: storage of the links
 // (widened to the compute type of S on load; FP32 and BF16 links are stored
 // as two rows, planes [mu][6][V], and completed by third_row).
 template <class S, int MU, bool FWD, bool ADD, int CT, bool NT = false, class SC = S, bool LT = false>
 __device__ __forceinline__ void hop_all(cx<typename S::R> (&acc)[CT][12], const typename SC::P* __restrict__ Uk,
                                         const typename S::P* __restrict__ Xc, uint32_t link_off, uint32_t nb_off,
-                                        size_t V, size_t KS, typename S::R invk = 0, bool neg = false,
-                                        size_t LS = 0) {
+                                        size_t V, size_t cs, size_t KS, typename S::R invk = 0,
+                                        bool neg = false, size_t LS = 0) {
     using R = typename S::R;
     // keep each direction's loads and arithmetic together: without this fence
     // the scheduler hoists the loads of all eight directions and spills
@@ -207,9 +207,8 @@ __device__ __forceinline__ void hop_all(cx<typename S::R> (&acc)[CT][12], const 
 #pragma unroll
     for (int c = 0; c < CT; ++c) {
         cx<R> p[12];
-        const typename S::P* xc = Xc + (size_t)c * 12 * V;
-#pragma unroll
-        for (int k = 0; k < 12; ++k) p[k] = NT ? S::ldb_nt(xc + (size_t)k * KS, nb_off) : S::ldb(xc + (size_t)k * KS, nb_off);
+        const typename S::P* xc = Xc + (size_t)c * cs;
+        Vec<S>::template load<NT>(p, xc, KS, 0, nb_off);
         hop_dir<R, MU, FWD, ADD>(acc[c], u, p);
     }
 }
@@ -238,8 +237,8 @@ __global__ void __launch_bounds__(256)
     if (tile >= ntiles || s < 0) return;
     const int c0 = col_begin + tile * CT;
     const size_t V = g.V;
-    const size_t cs = 12 * V;        // column stride of a block vector
-    const size_t KS = vec_plane(g);  // its plane stride (standard or tiled layout)
+    const size_t cs = Vec<SF>::col(g);    // column stride of the input blocks
+    const size_t KS = Vec<SF>::plane(g);  // their plane stride
 
     const int x = s % g.lx;
     const int y = (s / g.lx) % g.ly;
@@ -250,10 +249,11 @@ __global__ void __launch_bounds__(256)
     const int n_bz = (z == 0) ? s + (g.lz - 1) * g.sxy : s - g.sxy;
     const int n_bt = (t == 0) ? s + (g.lt - 1) * g.sxyz : s - g.sxyz;
     // byte offsets of the sites in a plane of the block vector
-    const uint32_t PB = sizeof(PF);
-    const auto vo = [&](int n) -> uint32_t { return vec_site(g, n) * PB; };
+    const auto vo = [&](int n) -> uint32_t { return Vec<SF>::off(g, n); };
     const uint32_t o_s = vo(s);
-    const uint32_t o_y = vec_site(g, s) * (uint32_t)sizeof(PY);  // the output may have another pair size
+    // the output may have another storage
+    const uint32_t o_y = Vec<SY>::off(g, s);
+    const size_t csy = Vec<SY>::col(g), KSy = Vec<SY>::plane(g);
     const uint32_t o_fx = vo((x == g.lx - 1) ? s - (g.lx - 1) : s + 1);
     const uint32_t o_bx = vo(n_bx);
     const uint32_t o_fy = vo((y == g.ly - 1) ? s - (g.ly - 1) * g.lx : s + g.lx);
@@ -286,8 +286,7 @@ __global__ void __launch_bounds__(256)
 #pragma unroll
             for (int c = 0; c < CT; ++c) {
                 cx<R> v[6];
-#pragma unroll
-                for (int k = 0; k < 6; ++k) v[k] = SF::ldb(Xc + (size_t)c * cs + (size_t)(6 * chir + k) * KS, o_s);
+                Vec<SF>::template load<false>(v, Xc + (size_t)c * cs, KS, 6 * chir, o_s);
 #pragma unroll
                 for (int i = 0; i < 6; ++i) {
                     cx<R> r = {R(0), R(0)};
@@ -301,9 +300,7 @@ __global__ void __launch_bounds__(256)
         const PF* Rc = Rh + (size_t)c0 * cs;
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
-#pragma unroll
-            for (int k = 0; k < 12; ++k)
-                acc[c][k] = SF::ldb_nt(Rc + (size_t)c * cs + (size_t)k * KS, o_s);
+            Vec<SF>::template load<true>(acc[c], Rc + (size_t)c * cs, KS, 0, o_s);
         }
     }
 
@@ -312,22 +309,21 @@ __global__ void __launch_bounds__(256)
     // (the forward link of t = Lt - 1, the backward link seen from t = 0)
     const R invk = (R)invk_d;
     const bool neg_ft = bc_t && t == g.lt - 1, neg_bt = bc_t && t == 0;
-    hop_all<SF, 0, true, ADD, CT, false, SC, LT>(acc, Uk, Xc, co(s), o_fx, V, KS, invk, false, CKS);
-    hop_all<SF, 0, false, ADD, CT, false, SC, LT>(acc, Uk, Xc, co(n_bx), o_bx, V, KS, invk, false, CKS);
-    hop_all<SF, 1, true, ADD, CT, false, SC, LT>(acc, Uk, Xc, co(s), o_fy, V, KS, invk, false, CKS);
-    hop_all<SF, 1, false, ADD, CT, false, SC, LT>(acc, Uk, Xc, co(n_by), o_by, V, KS, invk, false, CKS);
-    hop_all<SF, 2, true, ADD, CT, false, SC, LT>(acc, Uk, Xc, co(s), o_fz, V, KS, invk, false, CKS);
-    hop_all<SF, 2, false, ADD, CT, false, SC, LT>(acc, Uk, Xc, co(n_bz), o_bz, V, KS, invk, false, CKS);
-    hop_all<SF, 3, true, ADD, CT, (NTP & 2) != 0, SC, LT>(acc, Uk, Xc, co(s), o_ft, V, KS, invk, neg_ft, CKS);
-    hop_all<SF, 3, false, ADD, CT, (NTP & 2) != 0, SC, LT>(acc, Uk, Xc, co(n_bt), o_bt, V, KS, invk, neg_bt, CKS);
+    hop_all<SF, 0, true, ADD, CT, false, SC, LT>(acc, Uk, Xc, co(s), o_fx, V, cs, KS, invk, false, CKS);
+    hop_all<SF, 0, false, ADD, CT, false, SC, LT>(acc, Uk, Xc, co(n_bx), o_bx, V, cs, KS, invk, false, CKS);
+    hop_all<SF, 1, true, ADD, CT, false, SC, LT>(acc, Uk, Xc, co(s), o_fy, V, cs, KS, invk, false, CKS);
+    hop_all<SF, 1, false, ADD, CT, false, SC, LT>(acc, Uk, Xc, co(n_by), o_by, V, cs, KS, invk, false, CKS);
+    hop_all<SF, 2, true, ADD, CT, false, SC, LT>(acc, Uk, Xc, co(s), o_fz, V, cs, KS, invk, false, CKS);
+    hop_all<SF, 2, false, ADD, CT, false, SC, LT>(acc, Uk, Xc, co(n_bz), o_bz, V, cs, KS, invk, false, CKS);
+    hop_all<SF, 3, true, ADD, CT, (NTP & 2) != 0, SC, LT>(acc, Uk, Xc, co(s), o_ft, V, cs, KS, invk, neg_ft, CKS);
+    hop_all<SF, 3, false, ADD, CT, (NTP & 2) != 0, SC, LT>(acc, Uk, Xc, co(n_bt), o_bt, V, cs, KS, invk, neg_bt, CKS);
     __builtin_amdgcn_sched_barrier(0);
 
-    PY* Yc = Y + (size_t)c0 * cs;
+    PY* Yc = Y + (size_t)c0 * csy;
     if (MODE == APPLY) {
 #pragma unroll
         for (int c = 0; c < CT; ++c)
-#pragma unroll
-            for (int k = 0; k < 12; ++k) store_out<SY>(Yc + (size_t)c * cs + (size_t)k * KS, o_y, acc[c][k]);
+            Vec<SY>::template store<true>(Yc + (size_t)c * csy, KSy, o_y, acc[c]);
     } else {
 #pragma unroll
         for (int chir = 0; chir < 2; ++chir) {
@@ -336,11 +332,9 @@ __global__ void __launch_bounds__(256)
 #pragma unroll
             for (int c = 0; c < CT; ++c) {
                 {
-                    cx<R> xs[6];
+                    cx<R> xs[6], out[6];
                     if (MODE == JPOINT) {
-#pragma unroll
-                        for (int k = 0; k < 6; ++k)
-                            xs[k] = SF::ldb(Xc + (size_t)c * cs + (size_t)(6 * chir + k) * KS, o_s);
+                        Vec<SF>::template load<false>(xs, Xc + (size_t)c * cs, KS, 6 * chir, o_s);
                     }
 #pragma unroll
                     for (int i = 0; i < 6; ++i) {
@@ -357,11 +351,15 @@ __global__ void __launch_bounds__(256)
                                 if (j != i) q = q - T.at(i, j) * xs[j];
                             r = T.d[i] * q;
                         }
-                        store_out<SY>(Yc + (size_t)c * cs + (size_t)(6 * chir + i) * KS, o_y, r);
+                        out[i] = r;
                     }
+#pragma unroll
+                    for (int i = 0; i < 6; ++i) acc[c][6 * chir + i] = out[i];
                 }
             }
         }
+#pragma unroll
+        for (int c = 0; c < CT; ++c) Vec<SY>::template store<true>(Yc + (size_t)c * csy, KSy, o_y, acc[c]);
     }
 }
 
@@ -619,33 +617,42 @@ __global__ void __launch_bounds__(256)
     }
 }
 
-// FP32 / BF16 hop kernel for three or more columns (used for FP32): the LDS-staged
-// structure of k_hop_f64 in the compute type (float).  The staging rebuilds the third row of
-// every two-row link once per tile (instead of once per column tile) and widens
-// the links and the 6x6 blocks to float, 54 KB of LDS; the arithmetic and its
-// order are k_hop's, so the results are bit-identical to it.
-template <class SF, class SY, int MODE>
-__global__ void __launch_bounds__(256)
-    k_hop_lds_lp(const Geom g, const SiteMap sm, const typename SF::P* __restrict__ Uk,
-                 const typename SF::P* __restrict__ Cl, const typename SF::P* __restrict__ X,
+// FP32 / BF16 hop kernel for three or more columns: the LDS-staged structure of k_hop_f64 in
+// FP32 arithmetic.  The staging rebuilds the third row of every two-row link once per tile
+// (instead of once per column tile) and stores the links as float; the 6x6 blocks stay in their
+// storage format.  The arithmetic and its order are k_hop's (BF16 results are bit-identical to
+// it; in FP32 the third row's products contract in another order there).
+//
+// What bounds it is the way from the L2 to the registers (every neighbour spinor comes from the
+// L2, 0.8 - 1.4 GB per launch at 16^3 x 32, L = 12) and the waves that are there to wait for it:
+// the LDS is kept to 42 of the CU's 128 allocation units so that three workgroups fit a CU,
+// which in FP32 leaves no room for the first three planes of the blocks (kept in registers), and
+// NB neighbour spinors are in flight in their storage format; a direction's loads are issued as
+// soon as its buffer has been projected to the two-spinor.
+template <class SF, class SC, class SY, int MODE>
+__global__ void __launch_bounds__(256, 3)
+    k_hop_lds_lp(const Geom g, const SiteMap sm, const typename SC::P* __restrict__ Uk,
+                 const typename SC::P* __restrict__ Cl, const typename SF::P* __restrict__ X,
                  const typename SF::P* __restrict__ Rh, typename SY::P* __restrict__ Y, const int L,
                  const float invk, const int bc_t) {
     using R = typename SF::R;
     using PF = typename SF::P;
+    using PC = typename SC::P;
     static_assert(sizeof(R) == 4, "FP32 compute");
+    constexpr int NB = sizeof(PF) == 4 ? 4 : 2;  // neighbour spinors in flight: 48 registers
+    constexpr int TR = sizeof(PC) == 8 ? 3 : 0;  // planes of the blocks in registers
     __shared__ float2 sU[72][64];
-    __shared__ float2 sT[36][64];
+    __shared__ PC sT[36 - TR][64];
     const int lane = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.y);
     const int s0 = map_site(g, sm, blockIdx.x, lane);
     if (!__any(s0 >= 0)) return;  // the same for all four waves
     // a lane without a site takes lane 0's site (unpredicated stores, as in k_hop_f64)
     const int s = s0 >= 0 ? s0 : map_site(g, sm, blockIdx.x, 0);
-    const size_t V = g.V;
-    const size_t cs = 12 * V;         // column stride of a block vector
-    const size_t KS = vec_plane(g);   // its plane stride (standard or tiled layout)
+    const size_t cs = Vec<SF>::col(g);    // column stride of the input blocks
+    const size_t KS = Vec<SF>::plane(g);  // their plane stride
     const int x = s % g.lx, y = (s / g.lx) % g.ly, z = (s / g.sxy) % g.lz, t = s / g.sxyz;
-    constexpr uint32_t PB = sizeof(PF);
+    constexpr uint32_t PB = sizeof(PC);
     int nb[8];  // the neighbours x+, x-, y+, y-, z+, z-, t+, t-
     nb[0] = (x == g.lx - 1) ? s - (g.lx - 1) : s + 1;
     nb[1] = (x == 0) ? s + (g.lx - 1) : s - 1;
@@ -657,11 +664,12 @@ __global__ void __launch_bounds__(256)
     nb[7] = (t == 0) ? s + (g.lt - 1) * g.sxyz : s - g.sxyz;
     uint32_t on[8];  // byte offsets of the neighbours' spinors inside a plane of a column
 #pragma unroll
-    for (int d = 0; d < 8; ++d) on[d] = vec_site(g, nb[d]) * PB;
-    const uint32_t o_s = vec_site(g, s) * PB;
+    for (int d = 0; d < 8; ++d) on[d] = Vec<SF>::off(g, nb[d]);
+    const uint32_t o_s = Vec<SF>::off(g, s);
     // the site in the coefficient fields (two-row links: 24 planes; blocks: 36)
     const size_t CKS = coef_plane<PB>(g);
     const uint32_t c_s = coef_site<PB>(g, s, 24) * PB, t_s = coef_site<PB>(g, s, 36) * PB;
+    PC tr[TR > 0 ? TR : 1];
     {
         // wave mu: the two stored rows of U_mu(x) and U_mu(x - mu), completed by third_row (the
         // antiperiodic sign of the time links on the last slice, seen from t = Lt - 1 forward and
@@ -671,21 +679,26 @@ __global__ void __launch_bounds__(256)
         cx<R> uf[9], ub[9];
 #pragma unroll
         for (int k = 0; k < 6; ++k) {
-            const PF* pl = Uk + (size_t)(w * 6 + k) * CKS;
-            uf[k] = SF::ldb(pl, c_s);
-            ub[k] = SF::ldb(pl, ob);
+            const PC* pl = Uk + (size_t)(w * 6 + k) * CKS;
+            uf[k] = SC::ldb(pl, c_s);
+            ub[k] = SC::ldb(pl, ob);
         }
+        const auto raw_t = [&](int p) {
+            return *reinterpret_cast<const PC*>(reinterpret_cast<const char*>(Cl + (size_t)p * CKS) + t_s);
+        };
+#pragma unroll
+        for (int j = 0; j < 9; ++j) {
+            const int p = w * 9 + j;
+            if (p >= TR) sT[p - TR][lane] = raw_t(p);
+        }
+#pragma unroll
+        for (int j = 0; j < TR; ++j) tr[j] = raw_t(j);
         third_row<R>(uf, invk, neg_f);
         third_row<R>(ub, invk, neg_b);
 #pragma unroll
         for (int k = 0; k < 9; ++k) {
             sU[(2 * w) * 9 + k][lane] = make_float2(uf[k].re, uf[k].im);
             sU[(2 * w + 1) * 9 + k][lane] = make_float2(ub[k].re, ub[k].im);
-        }
-#pragma unroll
-        for (int j = 0; j < 9; ++j) {
-            const cx<R> v = SF::ldb_nt(Cl + (size_t)(w * 9 + j) * CKS, t_s);
-            sT[w * 9 + j][lane] = make_float2(v.re, v.im);
         }
     }
     __syncthreads();
@@ -696,17 +709,15 @@ __global__ void __launch_bounds__(256)
         const PF* xc = X + (size_t)c * cs;
         cx<R> acc[12];
         auto herm = [&](Herm6<StF32>& T, int chir) {
+            auto plane = [&](int p) { return SC::ld(p < TR ? &tr[p < TR ? p : 0] : &sT[p - TR][ln], 0); };
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
-                const float2 q = sT[chir * 18 + i][ln];
-                T.d[2 * i] = q.x;
-                T.d[2 * i + 1] = q.y;
+                const cx<R> q = plane(chir * 18 + i);
+                T.d[2 * i] = q.re;
+                T.d[2 * i + 1] = q.im;
             }
 #pragma unroll
-            for (int q = 0; q < 15; ++q) {
-                const float2 v = sT[chir * 18 + 3 + q][ln];
-                T.o[q] = {v.x, v.y};
-            }
+            for (int q = 0; q < 15; ++q) T.o[q] = plane(chir * 18 + 3 + q);
         };
         if (MODE == APPLY) {
 #pragma unroll
@@ -714,8 +725,7 @@ __global__ void __launch_bounds__(256)
                 Herm6<StF32> T;
                 herm(T, chir);
                 cx<R> v[6];
-#pragma unroll
-                for (int k = 0; k < 6; ++k) v[k] = SF::ldb(xc + (size_t)(6 * chir + k) * KS, o_s);
+                Vec<SF>::template load<false>(v, xc, KS, 6 * chir, o_s);
 #pragma unroll
                 for (int i = 0; i < 6; ++i) {
                     cx<R> r = {R(0), R(0)};
@@ -726,43 +736,58 @@ __global__ void __launch_bounds__(256)
             }
         } else {
             const PF* rc = Rh + (size_t)c * cs;
-#pragma unroll
-            for (int k = 0; k < 12; ++k) acc[k] = SF::ldb_nt(rc + (size_t)k * KS, o_s);
+            Vec<SF>::template load<true>(acc, rc, KS, 0, o_s);
         }
-        cx<R> p[2][12];
-        auto load_dir = [&](cx<R>(&dst)[12], int d) {
-#pragma unroll
-            for (int k = 0; k < 12; ++k)
-                dst[k] = (d >= 6) ? SF::ldb_nt(xc + (size_t)k * KS, on[d]) : SF::ldb(xc + (size_t)k * KS, on[d]);
+        typename SF::Raw p[NB][12];
+        // planes k .. k + G - 1 of the neighbour spinor of direction d
+        constexpr int G = Vec<SF>::G;
+        auto load_planes = [&](int d, int k) {
+            if (d >= 6) Vec<SF>::template load_group<true>(&p[d % NB][k], xc, k, on[d]);
+            else Vec<SF>::template load_group<false>(&p[d % NB][k], xc, k, on[d]);
         };
-        load_dir(p[0], 0);
+        // the first NB directions plane by plane: x+ and x- of a plane share their lines
+#pragma unroll
+        for (int k = 0; k < 12; k += G)
+#pragma unroll
+            for (int d = 0; d < NB; ++d) load_planes(d, k);
         static_for<0, 8>([&](auto dc) {
             constexpr int D = decltype(dc)::value;
             __builtin_amdgcn_sched_barrier(0);
-            if constexpr (D + 1 < 8) load_dir(p[(D + 1) % 2], D + 1);
             cx<R> u[9];
 #pragma unroll
             for (int k = 0; k < 9; ++k) {
                 const float2 v = sU[D * 9 + k][ln];
                 u[k] = {v.x, v.y};
             }
-            hop_dir<R, D / 2, (D % 2) == 0, ADD>(acc, u, p[D % 2]);
+            cx<R> h0[3], h1[3];
+            {
+                cx<R> q[12];
+#pragma unroll
+                for (int k = 0; k < 12; ++k) q[k] = SF::val(p[D % NB][k]);
+                project<R, D / 2, (D % 2) == 0>(q, h0, h1);
+            }
+            if constexpr (D + NB < 8) {
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int k = 0; k < 12; k += G) load_planes(D + NB, k);
+            }
+            hop_mul_acc<R, D / 2, (D % 2) == 0, ADD>(acc, u, h0, h1);
         });
         __builtin_amdgcn_sched_barrier(0);
-        typename SY::P* yc = Y + (size_t)c * cs;
-        const uint32_t o_y = vec_site(g, s) * (uint32_t)sizeof(typename SY::P);
+        typename SY::P* yc = Y + (size_t)c * Vec<SY>::col(g);
+        const uint32_t o_y = Vec<SY>::off(g, s);
+        const size_t KSy = Vec<SY>::plane(g);
         if (MODE == APPLY) {
-#pragma unroll
-            for (int k = 0; k < 12; ++k) store_out<SY>(yc + (size_t)k * KS, o_y, acc[k]);
+            Vec<SY>::template store<true>(yc, KSy, o_y, acc);
         } else {
+            cx<R> out[12];
 #pragma unroll
             for (int chir = 0; chir < 2; ++chir) {
                 Herm6<StF32> T;
                 herm(T, chir);
                 cx<R> xs[6];
                 if (MODE == JPOINT) {
-#pragma unroll
-                    for (int k = 0; k < 6; ++k) xs[k] = SF::ldb(xc + (size_t)(6 * chir + k) * KS, o_s);
+                    Vec<SF>::template load<false>(xs, xc, KS, 6 * chir, o_s);
                 }
 #pragma unroll
                 for (int i = 0; i < 6; ++i) {
@@ -778,17 +803,18 @@ __global__ void __launch_bounds__(256)
                             if (j != i) q = q - T.at(i, j) * xs[j];
                         r = T.d[i] * q;
                     }
-                    store_out<SY>(yc + (size_t)(6 * chir + i) * KS, o_y, r);
+                    out[6 * chir + i] = r;
                 }
             }
+            Vec<SY>::template store<true>(yc, KSy, o_y, out);
         }
     }
 }
 
 // First Jacobi sweep from G_0 = 0: Y = A_D^{-1} R (site-local, no hop).
 // SI: input storage, SF: compute (and clover) storage, SY: output storage,
-// SC: clover storage when it differs from SF (widened on load); with
-// RL != nullptr the input is also written out in format SF (the
+// SC: clover storage when it differs from SF (widened on load); with a
+// library block as output the input is also written to RL in format SF (the
 // low-precision copy of the right-hand side used by later sweeps).
 template <class SI, class SF, class SY, int MODE, class SC = SF>
 __global__ void __launch_bounds__(256)
@@ -796,34 +822,53 @@ __global__ void __launch_bounds__(256)
                   typename SF::P* __restrict__ RL, typename SY::P* __restrict__ Y, const int L) {
     // one thread per site; the site's A_D^{-1} block stays in registers for all L columns
     using R = typename SF::R;
-    const size_t V = g.V;
     const int s = blockIdx.x * 256 + threadIdx.x;
     if (s >= g.V) return;
-    const size_t cs = 12 * V;        // column stride of a block vector
-    const size_t KS = vec_plane(g);  // its plane stride (standard or tiled layout)
-    const uint32_t vs = vec_site(g, s);
-    const uint32_t oF = vs * sizeof(typename SF::P);
-    const uint32_t oI = vs * sizeof(typename SI::P);
-    const uint32_t oY = vs * sizeof(typename SY::P);
+    const uint32_t oF = Vec<SF>::off(g, s), oI = Vec<SI>::off(g, s), oY = Vec<SY>::off(g, s);
+    const size_t kF = Vec<SF>::plane(g), kI = Vec<SI>::plane(g), kY = Vec<SY>::plane(g);
     constexpr int PC = sizeof(typename SC::P);
     const uint32_t oC = coef_site<PC>(g, s, 36) * PC;
     const size_t CKS = coef_plane<PC>(g);
+    if constexpr (Vec<SY>::G > 1) {
+        // library output: whole spinors, both blocks in registers
+        Herm6<SC, R> T[2];
+        T[0].load(Cl, 0, oC, CKS);
+        T[1].load(Cl, 1, oC, CKS);
+        for (int col = 0; col < L; ++col) {
+            cx<typename SI::R> in[12];
+            Vec<SI>::template load<true>(in, Rin + (size_t)col * Vec<SI>::col(g), kI, 0, oI);
+            cx<R> v[12], o[12];
+#pragma unroll
+            for (int k = 0; k < 12; ++k) v[k] = {(R)in[k].re, (R)in[k].im};
+            // later sweeps read the rounded copy; the same rounded value is used here
+            Vec<SF>::template store<false>(RL + (size_t)col * Vec<SF>::col(g), kF, oF, v);
+#pragma unroll
+            for (int r = 0; r < 12; ++r) v[r] = SF::rnd(v[r]);
+#pragma unroll
+            for (int r = 0; r < 12; ++r) {
+                o[r] = {R(0), R(0)};
+                if (MODE == JBLOCK) {
+#pragma unroll
+                    for (int j = 0; j < 6; ++j) cfma(o[r], T[r / 6].at(r % 6, j), v[r / 6 * 6 + j]);
+                } else {
+                    o[r] = T[r / 6].d[r % 6] * v[r];
+                }
+            }
+            Vec<SY>::template store<true>(Y + (size_t)col * Vec<SY>::col(g), kY, oY, o);
+        }
+        return;
+    }
 #pragma unroll
     for (int chir = 0; chir < 2; ++chir) {
         Herm6<SC, R> T;
         T.load(Cl, chir, oC, CKS);
         for (int col = 0; col < L; ++col) {
-            const typename SI::P* Rc = Rin + (size_t)col * cs;
+            const typename SI::P* Rc = Rin + (size_t)col * Vec<SI>::col(g);
             cx<R> v[6];
 #pragma unroll
             for (int k = 0; k < 6; ++k) {
-                const auto w = SI::ldb_nt(Rc + (size_t)(6 * chir + k) * KS, oI);
+                const auto w = SI::ldb_nt(Rc + (size_t)(6 * chir + k) * kI, oI);
                 v[k] = {(R)w.re, (R)w.im};
-                if (RL != nullptr) {
-                    // later sweeps read the rounded copy; use the same rounded value here
-                    SF::stb(RL + (size_t)col * cs + (size_t)(6 * chir + k) * KS, oF, v[k]);
-                    v[k] = SF::rnd(v[k]);
-                }
             }
 #pragma unroll
             for (int r = 0; r < 6; ++r) {
@@ -834,34 +879,16 @@ __global__ void __launch_bounds__(256)
                 } else {
                     o = T.d[r] * v[r];
                 }
-                store_out<SY>(Y + (size_t)col * cs + (size_t)(6 * chir + r) * KS, oY, o);
+                store_out<SY>(Y + (size_t)col * Vec<SY>::col(g) + Vec<SY>::at(kY, 6 * chir + r), oY, o);
             }
         }
     }
-}
-
-template <class S>
-__global__ void k_from_lowp(const typename S::P* __restrict__ src, double2* __restrict__ dst, size_t n) {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const auto v = S::ld(src, i);
-    dst[i] = make_double2((double)v.re, (double)v.im);
 }
 
 // Streaming-load policy of the hop kernel: the time-direction neighbours are
 // streamed (measured about 5 % faster at 32^3 x 64, L = 12 than no streaming,
 // streaming the clover as well, or both).
 constexpr int kHopNTP = 2;
-
-// Columns per thread for L right-hand sides.  FP32 / BF16 storage takes
-// four-column tiles from L = 10 on (measured a few per cent faster than three
-// at L = 12; FP64 is fastest with three).
-int tile_cols(int L, bool lowp) {
-    if (L <= 2) return 1;
-    if (L <= 8) return 2;
-    if (L <= 12) return (lowp && L >= 10) ? 4 : 3;
-    return 4;
-}
 
 // What the compressed links need besides the field: 1/kappa and the time boundary condition.
 struct LinkInfo {
@@ -870,40 +897,25 @@ struct LinkInfo {
 };
 LinkInfo link_info(const wd_ctx* c) { return {c->kappa != 0.0 ? 1.0 / c->kappa : 0.0, c->bc_t}; }
 
-template <class SF, class SY, int MODE, int CT, class SC = SF>
+// k_hop on ntiles tiles of CT columns from col_begin on, a tile per wave.
+template <class SF, class SY, int MODE, int CT, class SC>
 hipError_t launch_hop_ct(const Geom& g, const LinkInfo& li, const void* Uk, const void* Cl, const void* X,
                          const void* Rh, void* Y, int col_begin, int ntiles, hipStream_t s) {
     if (ntiles > 4) return hipErrorInvalidValue;  // at most 4 wavefronts (256 threads) per site tile
-    const double bytes_site = 12.0 * CT * ntiles * sizeof(typename SF::P) + 72.0 * sizeof(typename SC::P);
-    const SiteMap sm = make_site_map(g, bytes_site);
-    dim3 block(64, ntiles), grid(sm.nblk);
-    using PF = typename SF::P;
-    using PY = typename SY::P;
-    using PC = typename SC::P;
-    k_hop<SF, SY, CT, MODE, kHopNTP, SC><<<grid, block, 0, s>>>(g, sm, (const PC*)Uk, (const PC*)Cl, (const PF*)X,
-                                                             (const PF*)Rh, (PY*)Y, col_begin, ntiles, li.invk,
-                                                             li.bc_t);
+    const SiteMap sm =
+        make_site_map(g, 12.0 * CT * ntiles * sizeof(typename SF::P) + 72.0 * sizeof(typename SC::P));
+    k_hop<SF, SY, CT, MODE, kHopNTP, SC><<<sm.nblk, dim3(64, ntiles), 0, s>>>(
+        g, sm, (const typename SC::P*)Uk, (const typename SC::P*)Cl, (const typename SF::P*)X,
+        (const typename SF::P*)Rh, (typename SY::P*)Y, col_begin, ntiles, li.invk, li.bc_t);
     return hipGetLastError();
 }
 
-template <class SF, class SY, int MODE, class SC = SF>
-hipError_t launch_hop_cols(const Geom& g, const LinkInfo& li, const void* Uk, const void* Cl, const void* X,
-                           const void* Rh, void* Y, int CT, int col_begin, int ntiles, hipStream_t s) {
-    switch (CT) {
-        case 1: return launch_hop_ct<SF, SY, MODE, 1, SC>(g, li, Uk, Cl, X, Rh, Y, col_begin, ntiles, s);
-        case 2: return launch_hop_ct<SF, SY, MODE, 2, SC>(g, li, Uk, Cl, X, Rh, Y, col_begin, ntiles, s);
-        case 3: return launch_hop_ct<SF, SY, MODE, 3, SC>(g, li, Uk, Cl, X, Rh, Y, col_begin, ntiles, s);
-        case 4: return launch_hop_ct<SF, SY, MODE, 4, SC>(g, li, Uk, Cl, X, Rh, Y, col_begin, ntiles, s);
-        default: return hipErrorInvalidValue;
-    }
-}
-
-// L columns: launches of up to four tiles of CT columns, then one launch for
-// the remainder (fewer than CT columns).
+// L columns: one or two with k_hop (a column per wave), three and more with the LDS-staged
+// kernels but for the BF16 case below.
 template <class SF, class SY, int MODE, class SC = SF>
 hipError_t launch_hop_t(const Geom& g, const LinkInfo& li, const void* Uk, const void* Cl, const void* X,
                         const void* Rh, void* Y, int L, hipStream_t s) {
-    if constexpr (std::is_same_v<SF, StF64> && std::is_same_v<SY, StF64>) {
+    if constexpr (std::is_same_v<SF, StF64>) {
         // FP64 vectors from three columns on: the LDS-staged kernel (measured faster at every
         // L >= 3 at 32^3 x 64; with one or two columns the staging cannot be shared by enough
         // waves); the links and blocks may be stored in FP32 or BF16 (SC)
@@ -924,29 +936,31 @@ hipError_t launch_hop_t(const Geom& g, const LinkInfo& li, const void* Uk, const
             return hipGetLastError();
         }
     }
-    if constexpr (std::is_same_v<SF, StF32> && std::is_same_v<SC, SF>) {
-        // FP32 from three columns on: the LDS-staged kernel (sweep 2.51 against 2.96 ms at
-        // 32^3 x 64, L = 12; BF16 keeps the register-tiled kernel, whose four-column tiles share
-        // each rebuilt link: 1.42 against 1.52 ms LDS-staged)
-        if (L >= 3) {
-            const SiteMap sm = make_site_map_rows(g, 12.0 * L * sizeof(typename SF::P) + 72.0 * 8);
+    if constexpr (sizeof(typename SF::P) < 16) {
+        // FP32 and BF16 from three columns on: the LDS-staged kernel, walking two (FP32) or four
+        // (BF16) t-slices together (3.6 and 5.5 % faster at 32^3 x 64, L = 12, than one; even
+        // at 16^3 x 32).  BF16 with up to six columns on 1024 tiles and more takes pairs of columns
+        // in k_hop instead, where the staging has too few columns to pay (six applications'
+        // sweeps at 24^3 x 48: 888 against 1063 us at L = 4, 1317 against 1493 at L = 6, 1702
+        // against 1768 at L = 8, but 384 against 367 at 16^3 x 32, L = 8; on 648 tiles and
+        // fewer the staged kernel is the faster one at every L).
+        const bool pairs = Vec<SF>::G == 4 && L <= 6 && ((long long)g.V + 63) / 64 >= 1024;
+        if (L >= 3 && !pairs) {
+            const SiteMap sm = make_site_map_rows(g, 12.0 * L * sizeof(typename SF::P) + 72.0 * 8, Vec<SF>::G);
             dim3 block(64, 4), grid(sm.nblk);
-            k_hop_lds_lp<SF, SY, MODE><<<grid, block, 0, s>>>(g, sm, (const typename SF::P*)Uk,
-                                                             (const typename SF::P*)Cl, (const typename SF::P*)X,
-                                                             (const typename SF::P*)Rh, (typename SY::P*)Y, L,
-                                                             (float)li.invk, li.bc_t);
+            k_hop_lds_lp<SF, SC, SY, MODE><<<grid, block, 0, s>>>(
+                g, sm, (const typename SC::P*)Uk, (const typename SC::P*)Cl, (const typename SF::P*)X,
+                (const typename SF::P*)Rh, (typename SY::P*)Y, L, (float)li.invk, li.bc_t);
             return hipGetLastError();
         }
     }
-    const int CT = tile_cols(L, sizeof(typename SF::P) < 16);
-    const int full = L / CT, rem = L % CT;
-    hipError_t e = hipSuccess;
-    for (int t0 = 0; t0 < full && e == hipSuccess; t0 += 4) {
-        const int nt = full - t0 < 4 ? full - t0 : 4;
-        e = launch_hop_cols<SF, SY, MODE, SC>(g, li, Uk, Cl, X, Rh, Y, CT, t0 * CT, nt, s);
+    if (L >= 3) {
+        // pairs of columns to a thread, then a last odd one
+        hipError_t e = launch_hop_ct<SF, SY, MODE, 2, SC>(g, li, Uk, Cl, X, Rh, Y, 0, L / 2, s);
+        if (e != hipSuccess || L % 2 == 0) return e;
+        return launch_hop_ct<SF, SY, MODE, 1, SC>(g, li, Uk, Cl, X, Rh, Y, L - 1, 1, s);
     }
-    if (e != hipSuccess || rem == 0) return e;
-    return launch_hop_cols<SF, SY, MODE, SC>(g, li, Uk, Cl, X, Rh, Y, rem, full * CT, 1, s);
+    return launch_hop_ct<SF, SY, MODE, 1, SC>(g, li, Uk, Cl, X, Rh, Y, 0, L, s);
 }
 
 template <class SI, class SF, class SY, class SC = SF>
@@ -1032,21 +1046,21 @@ hipError_t jacobi_coef(wd_ctx* c, int pi, const double2* R, double2* Z, int L, i
     return sweep_chain<SC>(c, pi, R, Z, tmp, out, L, j, s);
 }
 
-// j sweeps in storage format S (FP32 or BF16), FP64 in and out.
-template <class S>
+// j sweeps in storage format S (FP32 or BF16; links and blocks in SC), FP64 in and out.
+template <class S, class SC>
 hipError_t jacobi_lowp(wd_ctx* c, int pi, const double2* R, double2* Z, int L, int j, hipStream_t s) {
     const void* clf = (c->jacobi_kind == WD_JACOBI_POINT) ? c->f.Tp[pi] : c->f.Ti[pi];
     void* rl = c->lp[2];
-    if (j == 1) return launch_first<StF64, S, StF64>(c, clf, R, nullptr, Z, L, s);
-    hipError_t e = launch_first<StF64, S, S>(c, clf, R, rl, c->lp[0], L, s);
+    if (j == 1) return launch_first<StF64, S, StF64, SC>(c, clf, R, nullptr, Z, L, s);
+    hipError_t e = launch_first<StF64, S, S, SC>(c, clf, R, rl, c->lp[0], L, s);
     if (e != hipSuccess) return e;
     int cur = 0;
     for (int i = 2; i < j; ++i) {
-        e = launch_sweep<S, S>(c, pi, c->lp[cur], rl, c->lp[1 - cur], L, s);
+        e = launch_sweep<S, S, SC>(c, pi, c->lp[cur], rl, c->lp[1 - cur], L, s);
         if (e != hipSuccess) return e;
         cur = 1 - cur;
     }
-    return launch_sweep<S, StF64>(c, pi, c->lp[cur], rl, Z, L, s);
+    return launch_sweep<S, StF64, SC>(c, pi, c->lp[cur], rl, Z, L, s);
 }
 
 }  // namespace
@@ -1076,11 +1090,10 @@ hipError_t launch_sweep_coef(const wd_ctx* c, const double2* X, const double2* R
 }
 
 hipError_t launch_apply_A_lowp(wd_ctx* c, const double2* X, double2* Y, int L, Prec p, hipStream_t s) {
-    const size_t n = (size_t)12 * c->g.V * L;
-    hipError_t e = launch_to_lowp(X, c->lp[0], p, n, s);
+    hipError_t e = launch_to_lowp(X, c->lp[0], p, c->g, L, s);
     if (e != hipSuccess) return e;
     if (p == Prec::F32)
-        return launch_hop_t<StF32, StF64, APPLY>(c->g, link_info(c), c->f.Uk[1], c->f.Tc[1], c->lp[0], nullptr, Y, L,
+        return launch_hop_t<StF32P, StF64, APPLY, StF32>(c->g, link_info(c), c->f.Uk[1], c->f.Tc[1], c->lp[0], nullptr, Y, L,
                                                  s);
     return launch_hop_t<StBF16, StF64, APPLY>(c->g, link_info(c), c->f.Uk[2], c->f.Tc[2], c->lp[0], nullptr, Y, L, s);
 }
@@ -1095,8 +1108,8 @@ hipError_t launch_jacobi_coef(wd_ctx* c, const double2* R, double2* Z, int L, in
 hipError_t launch_jacobi(wd_ctx* c, const double2* R, double2* Z, int L, int j, Prec p, hipStream_t s) {
     const size_t n = (size_t)12 * c->g.V * L;
     if (j == 0) return launch_copy(Z, R, n, s);
-    if (p == Prec::F32) return jacobi_lowp<StF32>(c, 1, R, Z, L, j, s);
-    if (p == Prec::BF16) return jacobi_lowp<StBF16>(c, 2, R, Z, L, j, s);
+    if (p == Prec::F32) return jacobi_lowp<StF32P, StF32>(c, 1, R, Z, L, j, s);
+    if (p == Prec::BF16) return jacobi_lowp<StBF16, StBF16>(c, 2, R, Z, L, j, s);
     const void* clf = (c->jacobi_kind == WD_JACOBI_POINT) ? c->f.Tp[0] : c->f.Ti[0];
     // FP64: alternate between Z and the scratch block so that sweep j lands in Z
     double2* tmp = c->ws[10];
@@ -1112,19 +1125,18 @@ hipError_t launch_jacobi(wd_ctx* c, const double2* R, double2* Z, int L, int j, 
 // low-precision input and output (the output stays in the third buffer).
 hipError_t launch_hop_repeat_lowp(wd_ctx* c, const double2* X, const double2* R, double2* Y, int L, int mode, Prec p,
                                   int nrep, hipStream_t s) {
-    const size_t n = (size_t)12 * c->g.V * L;
     const int pi = p == Prec::F32 ? 1 : 2;
-    hipError_t e = launch_to_lowp(X, c->lp[0], p, n, s);
-    if (e == hipSuccess && mode == 1) e = launch_to_lowp(R, c->lp[2], p, n, s);
+    hipError_t e = launch_to_lowp(X, c->lp[0], p, c->g, L, s);
+    if (e == hipSuccess && mode == 1) e = launch_to_lowp(R, c->lp[2], p, c->g, L, s);
     for (int i = 0; i < nrep && e == hipSuccess; ++i) {
         if (mode == 0)
             e = p == Prec::F32
-                    ? launch_hop_t<StF32, StF64, APPLY>(c->g, link_info(c), c->f.Uk[1], c->f.Tc[1], c->lp[0], nullptr,
+                    ? launch_hop_t<StF32P, StF64, APPLY, StF32>(c->g, link_info(c), c->f.Uk[1], c->f.Tc[1], c->lp[0], nullptr,
                                                         Y, L, s)
                     : launch_hop_t<StBF16, StF64, APPLY>(c->g, link_info(c), c->f.Uk[2], c->f.Tc[2], c->lp[0],
                                                          nullptr, Y, L, s);
         else
-            e = p == Prec::F32 ? launch_sweep<StF32, StF32>(c, pi, c->lp[0], c->lp[2], c->lp[1], L, s)
+            e = p == Prec::F32 ? launch_sweep<StF32P, StF32P, StF32>(c, pi, c->lp[0], c->lp[2], c->lp[1], L, s)
                                : launch_sweep<StBF16, StBF16>(c, pi, c->lp[0], c->lp[2], c->lp[1], L, s);
     }
     return e;

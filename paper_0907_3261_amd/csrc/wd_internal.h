@@ -149,12 +149,22 @@ struct StBF16 {
     __device__ __forceinline__ static void st(P* p, size_t i, cx<R> v) {
         p[i] = pack_bf16(v.re, v.im);
     }
+    using Raw = uint32_t;  // a loaded pair, and its value
+    __device__ __forceinline__ static cx<R> val(Raw v) {
+        return {__uint_as_float(v << 16), __uint_as_float(v & 0xffff0000u)};
+    }
     // value after a round trip through the storage format
     __device__ __forceinline__ static cx<R> rnd(cx<R> v) {
         const uint32_t b = pack_bf16(v.re, v.im);
         return {__uint_as_float(b << 16), __uint_as_float(b & 0xffff0000u)};
     }
     WD_BYTE_OFFSET_ACCESSORS
+};
+
+// FP32 block vectors inside the library (StF32P; StF32 is the storage of links and blocks).
+struct StF32P : StF32 {
+    using Raw = cx<float>;  // a loaded pair, and its value
+    __device__ __forceinline__ static cx<R> val(Raw v) { return v; }
 };
 
 // Compile-time loop: f(std::integral_constant<int, D>) for D = D0 .. N - 1, so
@@ -204,8 +214,116 @@ __host__ __device__ __forceinline__ uint32_t vec_site(const Geom& g, int s) {
 __host__ __device__ __forceinline__ size_t vec_plane(const Geom& g) {
     return (g.vt & kVecTiled) ? (size_t)64 : (size_t)g.V;
 }
+// plane k and site of row r of a column, in the layout of g
+__host__ __device__ __forceinline__ void row_of(const Geom& g, size_t r, int& k, int& s) {
+    if (g.vt & kVecTiled) {
+        const uint32_t tile = (uint32_t)(r / 768), q = (uint32_t)(r - (size_t)tile * 768);
+        k = (int)(q >> 6);
+        s = (int)(tile * 64 + (q & 63));
+    } else {
+        k = (int)(r / (size_t)g.V);
+        s = (int)(r - (size_t)k * g.V);
+    }
+}
 // the tiled layout needs whole tiles and 32-bit byte offsets inside an FP64 column
 inline bool tiled_ok(const Geom& g) { return g.V % 64 == 0 && (long long)g.V * 192 <= 0xFFFFFFFFLL; }
+
+// Addressing of a block vector in storage S.  FP64 blocks are the caller's, in the layout of g.
+// FP32 (StF32P) and BF16 blocks (the low-precision Jacobi iterates, the learned layers'
+// activations and gradients) live inside the library: always tiled, the last tile padded where
+// V is not a multiple of 64, and G planes interleaved so that a lane loads G planes of its site as
+// one 16-byte word (two in FP32, four in BF16): pair (k, s) of a tile at 64 G (k / G) + G s + k % G.
+// A wavefront's 8-byte loads cost the L1 nearly as many cycles as 16-byte ones (measured on
+// L1-resident data: 16.7 clocks for 512 B, 18.6 for 1 KB, 4.7 for the 256 B of 4-byte loads), and
+// the kernels that wait for these loads issue a half or a quarter as many of them: FP32 sweeps at
+// 16^3 x 32, L = 12 took 122 us against 148 with one plane per load.
+// off: byte offset of site s inside a plane of a column; plane: what at() takes to give the pair
+// offset of plane k; col: column stride in pairs.
+typedef float wd_fvec4 __attribute__((ext_vector_type(4)));
+typedef uint32_t wd_uvec4 __attribute__((ext_vector_type(4)));
+inline __host__ __device__ size_t lowp_tiles(const Geom& g) { return ((size_t)g.V + 63) / 64; }
+template <class S>
+struct Vec {
+    using P = typename S::P;
+    using R = typename S::R;
+    static constexpr uint32_t PB = sizeof(P);
+    static constexpr int G = 16 / PB;
+    __device__ __forceinline__ static uint32_t off(const Geom& g, int s) {
+        if constexpr (G == 1) return vec_site(g, s) * PB;
+        return (uint32_t)(s >> 6) * (768 * PB) + (uint32_t)(s & 63) * 16;
+    }
+    __device__ __forceinline__ static size_t plane(const Geom& g) { return G == 1 ? vec_plane(g) : (size_t)64; }
+    __device__ __forceinline__ static size_t at(size_t KS, int k) {
+        return G == 1 ? (size_t)k * KS : (size_t)(k / G * (64 * G) + k % G);
+    }
+    __device__ __forceinline__ static size_t col(const Geom& g) {
+        return G == 1 ? (size_t)12 * g.V : (size_t)768 * lowp_tiles(g);
+    }
+    // planes k .. k + G - 1 (k a multiple of G) of the site at byte offset o, in their storage
+    // format, streamed with NT (library blocks only)
+    template <bool NT, class Raw>
+    __device__ __forceinline__ static void load_group(Raw* v, const P* base, int k, uint32_t o) {
+        const char* q = reinterpret_cast<const char*>(base + k * 64) + o;
+        if constexpr (G == 2) {
+            const wd_fvec4* f = reinterpret_cast<const wd_fvec4*>(q);
+            const wd_fvec4 w = NT ? __builtin_nontemporal_load(f) : *f;
+            v[0] = {w.x, w.y};
+            v[1] = {w.z, w.w};
+        } else {
+            const wd_uvec4* f = reinterpret_cast<const wd_uvec4*>(q);
+            const wd_uvec4 w = NT ? __builtin_nontemporal_load(f) : *f;
+            v[0] = w.x;
+            v[1] = w.y;
+            v[2] = w.z;
+            v[3] = w.w;
+        }
+    }
+    // planes k0 .. k0 + N - 1 of the site at byte offset o
+    template <bool NT, int N>
+    __device__ __forceinline__ static void load(cx<R> (&v)[N], const P* base, size_t KS, int k0, uint32_t o) {
+        if constexpr (G == 1) {
+#pragma unroll
+            for (int k = 0; k < N; ++k)
+                v[k] = NT ? S::ldb_nt(base + (size_t)(k0 + k) * KS, o) : S::ldb(base + (size_t)(k0 + k) * KS, o);
+        } else {
+#pragma unroll
+            for (int q = 0; q < 12; q += G) {
+                if (q + G <= k0 || q >= k0 + N) continue;
+                typename S::Raw r[G];
+                load_group<NT>(r, base, q, o);
+#pragma unroll
+                for (int i = 0; i < G; ++i)
+                    if (q + i >= k0 && q + i < k0 + N) v[q + i - k0] = S::val(r[i]);
+            }
+        }
+    }
+    // store planes 0 .. 11 of a site, streamed with NT
+    template <bool NT, typename RV>
+    __device__ __forceinline__ static void store(P* base, size_t KS, uint32_t o, const cx<RV> (&v)[12]) {
+#pragma unroll
+        for (int k = 0; k < 12; k += G) {
+            char* q = reinterpret_cast<char*>(base + (G == 1 ? (size_t)k * KS : (size_t)k * 64)) + o;
+            if constexpr (G == 1) {
+                const cx<R> w = {(R)v[k].re, (R)v[k].im};
+                if (NT) S::st_nt(reinterpret_cast<P*>(q), w);
+                else S::st(reinterpret_cast<P*>(q), 0, w);
+            } else if constexpr (G == 2) {
+                const wd_fvec4 w = {(float)v[k].re, (float)v[k].im, (float)v[k + 1].re, (float)v[k + 1].im};
+                if (NT) __builtin_nontemporal_store(w, reinterpret_cast<wd_fvec4*>(q));
+                else *reinterpret_cast<wd_fvec4*>(q) = w;
+            } else {
+                const wd_uvec4 w = {pack_bf16((float)v[k].re, (float)v[k].im), pack_bf16((float)v[k + 1].re, (float)v[k + 1].im),
+                                    pack_bf16((float)v[k + 2].re, (float)v[k + 2].im),
+                                    pack_bf16((float)v[k + 3].re, (float)v[k + 3].im)};
+                if (NT) __builtin_nontemporal_store(w, reinterpret_cast<wd_uvec4*>(q));
+                else *reinterpret_cast<wd_uvec4*>(q) = w;
+            }
+        }
+    }
+};
+// 32-bit byte offsets inside a column of a low-precision block (at 96 bytes per site in FP32; the
+// fields of a lattice this large do not fit the card's memory)
+inline bool lowp_ok(const Geom& g) { return (long long)lowp_tiles(g) * 64 * 96 <= 0xFFFFFFFFLL; }
 
 // The FP64 coefficient fields of the hop kernels (kappa-scaled links, T, T^{-1},
 // the point form; np planes of V pairs each) are kept tiled when the lattice
@@ -364,8 +482,8 @@ struct wd_ctx {
     double2* small = nullptr;     // L x L matrices, scalars (see wd_blas.hip)
     int* dstatus = nullptr;
     double* host_ctl = nullptr;   // pinned host mirror of per-iteration control data
-    // learned preconditioner: FP32 links (unscaled), weights, training workspace
-    float2* U32 = nullptr;
+    // learned preconditioner: FP32 links (unscaled, [36][re, im][V]), weights, training workspace
+    float* U32 = nullptr;
     float2* theta = nullptr;
     bool have_theta = false;
     void* learn_mem = nullptr;
@@ -382,8 +500,10 @@ hipError_t launch_clover(const double2* U, double2* T, double2* Ti, const Geom& 
 hipError_t launch_convert(const double2* src, void* dst, Prec p, double scale, size_t n, hipStream_t s);
 // point form of T: diagonal slots replaced by 1/diag, off-diagonal slots kept
 hipError_t launch_point_form(const double2* T, double2* Tp, size_t V, hipStream_t s);
-// convert an FP64 block vector to precision p and back
-hipError_t launch_to_lowp(const double2* src, void* dst, Prec p, size_t n, hipStream_t s);
+// an FP64 block vector of L columns (layout of g) into a library block of precision p
+hipError_t launch_to_lowp(const double2* src, void* dst, Prec p, const Geom& g, int L, hipStream_t s);
+// links into FP32 with separate real and imaginary planes, [36][2][V]
+hipError_t launch_links_f32(const double2* src, float* dst, size_t V, hipStream_t s);
 
 // ---- Wilson hopping kernels (wd_dslash.hip)
 // Y = A X (FP64)

@@ -23,18 +23,19 @@ namespace {
 constexpr int kNL = WD_LEARNED_LAYERS, kND = WD_LEARNED_DIRS;
 
 // S_d psi for one column at site s: returns 12 complex (index 3*spin + colour).  V:
-// sites (the links' plane stride); KS, vs, vnb: the plane stride of the block vector
-// and the element offsets of s and nb in it (standard or tiled layout).
+// sites (the links' plane stride); KS, ob: the plane stride of the block vector
+// and the byte offset of nb (s for d = 0) in it.
 template <class SZ>
-__device__ __forceinline__ void shifted(const float2* __restrict__ U, const typename SZ::P* __restrict__ Z, size_t V,
-                                        size_t KS, int d, int s, int nb, uint32_t vs, uint32_t vnb,
-                                        cx<float> (&q)[12]) {
+__device__ __forceinline__ void shifted(const float* __restrict__ U, const typename SZ::P* __restrict__ Z, size_t V,
+                                        size_t KS, int d, int s, int nb, uint32_t ob, cx<float> (&q)[12]) {
+    cx<typename SZ::R> z[12];
+    Vec<SZ>::template load<false>(z, Z, KS, 0, ob);
+    cx<float> p[12];
+#pragma unroll
+    for (int k = 0; k < 12; ++k) p[k] = {(float)z[k].re, (float)z[k].im};
     if (d == 0) {
 #pragma unroll
-        for (int k = 0; k < 12; ++k) {
-            const auto v = SZ::ld(Z, (size_t)k * KS + vs);
-            q[k] = {(float)v.re, (float)v.im};
-        }
+        for (int k = 0; k < 12; ++k) q[k] = p[k];
         return;
     }
     const int mu = (d - 1) >> 1;
@@ -42,12 +43,9 @@ __device__ __forceinline__ void shifted(const float2* __restrict__ U, const type
     const int ls = fwd ? s : nb;
     cx<float> u[9];
 #pragma unroll
-    for (int k = 0; k < 9; ++k) u[k] = StF32::ld(U, (size_t)(mu * 9 + k) * V + ls);
-    cx<float> p[12];
-#pragma unroll
-    for (int k = 0; k < 12; ++k) {
-        const auto v = SZ::ld(Z, (size_t)k * KS + vnb);
-        p[k] = {(float)v.re, (float)v.im};
+    for (int k = 0; k < 9; ++k) {
+        const float* ur = U + (size_t)(mu * 9 + k) * 2 * V;
+        u[k] = {ur[ls], ur[V + ls]};
     }
 #pragma unroll
     for (int sp = 0; sp < 4; ++sp)
@@ -145,9 +143,8 @@ __device__ __forceinline__ void term_apply(const Term<R, CT>& t, const float2* _
 // storage (and arithmetic precision) of the links.  W: 9 x 16 complex
 // (row-major 4 x 4 per direction; direction 1 + 2 mu is the forward hop,
 // 2 + 2 mu the backward one), FP32.  Columns [c0 + tile*CT, + CT) of the
-// block vectors; every tile of the launch is complete.  In FP32 the nine
-// terms are software-pipelined: the operands of the next term are in flight
-// while the current one is accumulated.
+// block vectors; every tile of the launch is complete.  Used for one or two
+// columns in FP64.
 template <class SI, class SO, class SL, int CT>
 __global__ void __launch_bounds__(256) k_layer(const Geom g, const SiteMap sm, const typename SL::P* __restrict__ U,
                                                const float2* __restrict__ W, const typename SI::P* __restrict__ Zin,
@@ -157,8 +154,7 @@ __global__ void __launch_bounds__(256) k_layer(const Geom g, const SiteMap sm, c
     const int s = map_site(g, sm, blockIdx.x, threadIdx.x);
     const int tile = blockIdx.y * blockDim.y + threadIdx.y;
     if (s < 0 || tile >= ntile) return;
-    const int x = s % g.lx, y = (s / g.lx) % g.ly, z = (s / g.sxy) % g.lz, t = s / g.sxyz;
-    const int co[4] = {x, y, z, t};
+    const int co[4] = {s % g.lx, (s / g.lx) % g.ly, (s / g.sxy) % g.lz, s / g.sxyz};
     const int ext[4] = {g.lx, g.ly, g.lz, g.lt};
     const int str[4] = {1, g.lx, g.sxy, g.sxyz};
     const size_t col0 = (size_t)(c0 + tile * CT);
@@ -173,33 +169,17 @@ __global__ void __launch_bounds__(256) k_layer(const Geom g, const SiteMap sm, c
     for (int c = 0; c < CT; ++c)
 #pragma unroll
         for (int k = 0; k < 12; ++k) acc[c][k] = {R(0), R(0)};
-    if constexpr (sizeof(R) == 4) {
-        // FP32: two operand sets, the next term's loads in flight during the current term
-        Term<R, CT> A, B;  // A: self and backward terms, B: forward terms
-        term_load<0, SI, SL>(A, U, 0, s, Zin, V, KS, col0, vo(s));
-        term_load<1, SI, SL>(B, U, 0, s, Zin, V, KS, col0, vo(fwd_site(0)));
-        term_apply<0>(A, W, acc);
+    // one operand set (two would halve the occupancy)
+    Term<R, CT> A;
+    term_load<0, SI, SL>(A, U, 0, s, Zin, V, KS, col0, vo(s));
+    term_apply<0>(A, W, acc);
 #pragma unroll 1
-        for (int mu = 0; mu < 4; ++mu) {
-            const int bw = bwd_site(mu);
-            term_load<2, SI, SL>(A, U, mu, bw, Zin, V, KS, col0, vo(bw));
-            term_apply<1>(B, W + (1 + 2 * mu) * 16, acc);
-            if (mu < 3) term_load<1, SI, SL>(B, U, mu + 1, s, Zin, V, KS, col0, vo(fwd_site(mu + 1)));
-            term_apply<2>(A, W + (2 + 2 * mu) * 16, acc);
-        }
-    } else {
-        // FP64: one operand set (two would halve the occupancy)
-        Term<R, CT> A;
-        term_load<0, SI, SL>(A, U, 0, s, Zin, V, KS, col0, vo(s));
-        term_apply<0>(A, W, acc);
-#pragma unroll 1
-        for (int mu = 0; mu < 4; ++mu) {
-            term_load<1, SI, SL>(A, U, mu, s, Zin, V, KS, col0, vo(fwd_site(mu)));
-            term_apply<1>(A, W + (1 + 2 * mu) * 16, acc);
-            const int bw = bwd_site(mu);
-            term_load<2, SI, SL>(A, U, mu, bw, Zin, V, KS, col0, vo(bw));
-            term_apply<2>(A, W + (2 + 2 * mu) * 16, acc);
-        }
+    for (int mu = 0; mu < 4; ++mu) {
+        term_load<1, SI, SL>(A, U, mu, s, Zin, V, KS, col0, vo(fwd_site(mu)));
+        term_apply<1>(A, W + (1 + 2 * mu) * 16, acc);
+        const int bw = bwd_site(mu);
+        term_load<2, SI, SL>(A, U, mu, bw, Zin, V, KS, col0, vo(bw));
+        term_apply<2>(A, W + (2 + 2 * mu) * 16, acc);
     }
 #pragma unroll
     for (int c = 0; c < CT; ++c) {
@@ -227,24 +207,23 @@ constexpr int kGB = 256;  // threads of the reduction kernels
 // partial[(col * gridDim.x + block) * 16 + e] = sum over this block's sites of
 //   2 sum_a g[3 s + a] conj((S_d z)[3 t + a]),  e = 4 s + t
 template <class SZ>
-__global__ void __launch_bounds__(kGB) k_wgrad(const Geom g, const float2* __restrict__ U,
+__global__ void __launch_bounds__(kGB) k_wgrad(const Geom g, const float* __restrict__ U,
                                                const typename SZ::P* __restrict__ Z, const float2* __restrict__ Gr,
                                                int d, double2* __restrict__ partial) {
     __shared__ double sh[kGB / 64][32];
-    const size_t V = g.V, KS = vec_plane(g);
+    const size_t V = g.V, KS = Vec<SZ>::plane(g);
     const int col = blockIdx.y;
-    const typename SZ::P* zc = Z + (size_t)col * 12 * V;
-    const float2* gc = Gr + (size_t)col * 12 * V;
+    const typename SZ::P* zc = Z + (size_t)col * Vec<SZ>::col(g);
+    const float2* gc = Gr + (size_t)col * Vec<StF32P>::col(g);
     double acc[32];
 #pragma unroll
     for (int e = 0; e < 32; ++e) acc[e] = 0.0;
     for (int s = blockIdx.x * kGB + threadIdx.x; s < g.V; s += gridDim.x * kGB) {
         cx<float> q[12], gv[12];
         const int nb = neighbour(g, s, d);
-        const uint32_t vs = vec_site(g, s);
-        shifted<SZ>(U, zc, V, KS, d, s, nb, vs, vec_site(g, nb), q);
-#pragma unroll
-        for (int k = 0; k < 12; ++k) gv[k] = StF32::ld(gc, (size_t)k * KS + vs);
+        shifted<SZ>(U, zc, V, KS, d, s, nb, Vec<SZ>::off(g, nb), q);
+        const uint32_t og = Vec<StF32P>::off(g, s);
+        Vec<StF32P>::load<false>(gv, gc, 64, 0, og);
 #pragma unroll
         for (int sp = 0; sp < 4; ++sp)
 #pragma unroll
@@ -298,9 +277,11 @@ __global__ void __launch_bounds__(kGB) k_reduce16(const double2* __restrict__ pa
     }
 }
 
-// g = (y - e) / (||e_col||^2 P) in FP32; partial[block] = sum |y - e|^2 / ||e_col||^2
-__global__ void __launch_bounds__(kGB) k_loss(const float2* __restrict__ Y, const double2* __restrict__ E,
-                                              const double* __restrict__ en2, size_t n_per_col, int L,
+// g = (y - e) / (||e_col||^2 P) in FP32; partial[block] = sum |y - e|^2 / ||e_col||^2.  The
+// elements are taken in the order of E's rows (the layout of geom); y and g are library blocks.
+__global__ void __launch_bounds__(kGB) k_loss(const Geom geom, const float2* __restrict__ Y,
+                                              const double2* __restrict__ E, const double* __restrict__ en2,
+                                              size_t n_per_col, int L,
                                               float2* __restrict__ Gr, double* __restrict__ partial) {
     __shared__ double sh[kGB / 64];
     const size_t n = n_per_col * L;
@@ -308,12 +289,16 @@ __global__ void __launch_bounds__(kGB) k_loss(const float2* __restrict__ Y, cons
     for (size_t i = (size_t)blockIdx.x * kGB + threadIdx.x; i < n; i += (size_t)gridDim.x * kGB) {
         const int col = (int)(i / n_per_col);
         const double inv = 1.0 / en2[col];
-        const float2 y = Y[i];
+        int k, site;
+        row_of(geom, i - (size_t)col * n_per_col, k, site);
+        const size_t base = (size_t)col * Vec<StF32P>::col(geom) + Vec<StF32P>::at(64, k);
+        const uint32_t off = Vec<StF32P>::off(geom, site);
+        const cx<float> y = StF32P::ldb(Y + base, off);
         const double2 e = E[i];
-        const double dr = (double)y.x - e.x, di = (double)y.y - e.y;
+        const double dr = (double)y.re - e.x, di = (double)y.im - e.y;
         acc += (dr * dr + di * di) * inv;
         const double sc = inv / L;
-        Gr[i] = make_float2((float)(dr * sc), (float)(di * sc));
+        StF32P::stb(Gr + base, off, {(float)(dr * sc), (float)(di * sc)});
     }
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
 #pragma unroll
@@ -362,19 +347,16 @@ __global__ void __launch_bounds__(kGB) k_res_loss(const double2* Ay, const doubl
     }
 }
 
-// FP32 activation -> FP64 block; gamma5 applied on request (the gradient's last factor)
-__global__ void k_to_f64(const float2* __restrict__ src, double2* __restrict__ dst, size_t n) {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) dst[i] = make_double2((double)src[i].x, (double)src[i].y);
-}
-__global__ void k_gamma5_to_f32(const double2* __restrict__ src, float2* __restrict__ dst, size_t n_per_col,
-                                size_t n, int tiled) {
+// gamma5 src (FP64, the layout of g) into an FP32 library block (the gradient's last factor)
+__global__ void k_gamma5_to_f32(const Geom g, const double2* __restrict__ src, float2* __restrict__ dst, size_t n) {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const size_t plane = n_per_col / 12, r = i % n_per_col;
-    const int k = tiled ? (int)((r % 768) / 64) : (int)(r / plane);
+    const size_t n_per_col = (size_t)12 * g.V, col = i / n_per_col;
+    int k, site;
+    row_of(g, i - col * n_per_col, k, site);
     const double sg = k >= 6 ? -1.0 : 1.0;
-    dst[i] = make_float2((float)(sg * src[i].x), (float)(sg * src[i].y));
+    StF32P::stb(dst + col * Vec<StF32P>::col(g) + Vec<StF32P>::at(64, k), Vec<StF32P>::off(g, site),
+                {(float)(sg * src[i].x), (float)(sg * src[i].y)});
 }
 
 __global__ void __launch_bounds__(kGB) k_reduce_loss(const double* __restrict__ partial, int np, int L,
@@ -497,36 +479,117 @@ __global__ void __launch_bounds__(256) k_layer_lds(const Geom g, const SiteMap s
     }
 }
 
-inline unsigned nblk(size_t n, unsigned b) { return (unsigned)((n + b - 1) / b); }
-
-template <class SI, class SO, class SL, int CT>
-hipError_t launch_layer_ct(const wd_ctx* c, const typename SL::P* U, const float2* W, const void* in, void* out,
-                           int c0, int ntile, hipStream_t s) {
-    if (ntile <= 0) return hipSuccess;
-    const int ty = ntile < 4 ? ntile : 4;
-    // XCD-aware site order in rows of the hop kernels' map, four t-slices walked together
-    // (a fifth to a third fewer fetched bytes than the plane-wide map at 32^3 x 64, L = 12)
-    const SiteMap sm =
-        make_site_map_rows(c->g, 12.0 * CT * ty * sizeof(typename SI::P) + 36.0 * sizeof(typename SL::P), 4);
-    dim3 block(64, ty), grid(sm.nblk, (ntile + ty - 1) / ty);
-    k_layer<SI, SO, SL, CT><<<grid, block, 0, s>>>(c->g, sm, U, W, (const typename SI::P*)in, (typename SO::P*)out,
-                                                   c0, ntile);
-    return hipGetLastError();
+// One FP32 layer.
+// LU: the links staged in LDS once per tile, as in k_layer_lds (wave mu stores U_mu(x) and
+// U_mu(x - mu), then wave w takes columns w, w + 4, ...), for three columns and more; else (one
+// or two columns, too few waves to share the staging) one column per wave, links read per term.
+template <class SI, class SO, bool LU>
+__global__ void __launch_bounds__(256) k_layer_f32(const Geom g, const SiteMap sm, const float* __restrict__ U,
+                                                   const float2* __restrict__ W, const typename SI::P* __restrict__ Zin,
+                                                   typename SO::P* __restrict__ Zout, const int L, const int cpg) {
+    __shared__ float2 sU[LU ? 72 : 1][64];
+    const size_t V = g.V;
+    const int lane = threadIdx.x;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.y);
+    const int s0 = map_site(g, sm, blockIdx.x, lane);
+    if (!__any(s0 >= 0)) return;  // the same for all four waves
+    const int s = s0 >= 0 ? s0 : map_site(g, sm, blockIdx.x, 0);
+    const int co[4] = {s % g.lx, (s / g.lx) % g.ly, (s / g.sxy) % g.lz, s / g.sxyz};
+    const int ext[4] = {g.lx, g.ly, g.lz, g.lt};
+    const int str[4] = {1, g.lx, g.sxy, g.sxyz};
+    uint32_t on[9];  // byte offset of each term's input site in a plane of a column
+    on[0] = Vec<SI>::off(g, s);
+    int nbw[4];
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) {
+        const int f = (co[mu] + 1 == ext[mu]) ? s - (ext[mu] - 1) * str[mu] : s + str[mu];
+        nbw[mu] = (co[mu] == 0) ? s + (ext[mu] - 1) * str[mu] : s - str[mu];
+        on[1 + 2 * mu] = Vec<SI>::off(g, f);
+        on[2 + 2 * mu] = Vec<SI>::off(g, nbw[mu]);
+    }
+    if constexpr (LU) {
+        const int bw = (wv == 0) ? nbw[0] : (wv == 1) ? nbw[1] : (wv == 2) ? nbw[2] : nbw[3];
+#pragma unroll
+        for (int k = 0; k < 9; ++k) {
+            const float* ur = U + (size_t)(wv * 9 + k) * 2 * V;
+            const float* ui = ur + V;
+            sU[(2 * wv) * 9 + k][lane] = make_float2(ur[(uint32_t)s], ui[(uint32_t)s]);
+            sU[(2 * wv + 1) * 9 + k][lane] = make_float2(ur[(uint32_t)bw], ui[(uint32_t)bw]);
+        }
+    }
+    const size_t KS = Vec<SI>::plane(g);
+    if constexpr (LU) __syncthreads();
+    auto column = [&](int c) {
+        // the LDS lane index is opaque per column so that the staged links are read where they
+        // are used instead of all being hoisted into registers
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        const typename SI::P* zc = Zin + (size_t)c * Vec<SI>::col(g);
+        cx<float> acc[1][12];
+#pragma unroll
+        for (int k = 0; k < 12; ++k) acc[0][k] = {0.f, 0.f};
+        // the next term's spinor (and link) in flight during the current term; an FP64 input is
+        // rounded where it is used, so that the rounding does not wait for the load
+        cx<typename SI::R> raw[2][12];
+        cx<float> link[2][9];
+        auto load_in = [&](auto dc) {
+            constexpr int D = decltype(dc)::value;
+            if constexpr (!LU && D > 0) {
+#pragma unroll
+                for (int k = 0; k < 9; ++k) {
+                    const float* ur = U + (size_t)((D - 1) / 2 * 9 + k) * 2 * V;
+                    const float* ui = ur + V;
+                    const uint32_t ls = (uint32_t)(D % 2 == 1 ? s : nbw[(D - 1) / 2]);
+                    link[D % 2][k] = {ur[ls], ui[ls]};
+                }
+            }
+            Vec<SI>::template load<false>(raw[D % 2], zc, KS, 0, on[D]);
+        };
+        load_in(std::integral_constant<int, 0>{});
+        static_for<0, kND>([&](auto dc) {
+            constexpr int D = decltype(dc)::value;
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (D + 1 < kND) load_in(std::integral_constant<int, D + 1>{});
+            Term<float, 1> cur;
+#pragma unroll
+            for (int k = 0; k < 12; ++k) cur.p[0][k] = {(float)raw[D % 2][k].re, (float)raw[D % 2][k].im};
+            if constexpr (D > 0) {
+#pragma unroll
+                for (int k = 0; k < 9; ++k) {
+                    if constexpr (LU) {
+                        const float2 v = sU[(D - 1) * 9 + k][ln];
+                        cur.u[k] = {v.x, v.y};
+                    } else {
+                        cur.u[k] = link[D % 2][k];
+                    }
+                }
+            }
+            term_apply<D == 0 ? 0 : (D % 2 == 1 ? 1 : 2)>(cur, W + D * 16, acc);
+        });
+        __builtin_amdgcn_sched_barrier(0);
+        typename SO::P* oc = Zout + (size_t)c * Vec<SO>::col(g);
+        const uint32_t oy = Vec<SO>::off(g, s);
+        const size_t KSy = Vec<SO>::plane(g);
+        Vec<SO>::template store<false>(oc, KSy, oy, acc[0]);
+    };
+    if constexpr (LU) {
+        const int c1 = min(L, (int)(blockIdx.y + 1) * cpg);
+        for (int c = blockIdx.y * cpg + wv; c < c1; c += 4) column(c);
+    } else {
+        column(wv);
+    }
 }
 
-// One layer over L columns, one column per thread.  At 32^3 x 64 with twelve
-// columns this is the fastest tiling in both precisions (two- and four-column
-// tiles lose occupancy to their accumulators and operand sets, and spill).
-constexpr int kLayerCT = 1;
+inline unsigned nblk(size_t n, unsigned b) { return (unsigned)((n + b - 1) / b); }
 
+// One FP64 layer over L columns.
 template <class SI, class SO, class SL>
 hipError_t launch_layer(const wd_ctx* c, const typename SL::P* U, const float2* W, const void* in, void* out, int L,
                         hipStream_t s) {
-    if (std::is_same_v<SL, StF64> && L >= 3) {
-        // FP64: LDS-staged links from three columns on (one workgroup per tile, all columns;
-        // measured 12.8 against 15.2 ms per application of M at 32^3 x 64, L = 12; in FP32 the
-        // register-tiled kernel with its next-term prefetch stays 3 % faster)
-        // the same site map as the register-tiled layer (16 % fewer fetched bytes and 5 % faster
+    if (L >= 3) {
+        // LDS-staged links from three columns on (one workgroup per tile, all columns; measured
+        // 12.8 against 15.2 ms per application of M at 32^3 x 64, L = 12), on the hop kernels'
+        // site map with four t-slices walked together (16 % fewer fetched bytes and 5 % faster
         // than the plane-wide map)
         const SiteMap sm = make_site_map_rows(c->g, 12.0 * L * sizeof(typename SI::P) + 72.0 * sizeof(typename SL::P), 4);
         dim3 block(64, 4), grid(sm.nblk);
@@ -534,12 +597,28 @@ hipError_t launch_layer(const wd_ctx* c, const typename SL::P* U, const float2* 
                                                        (typename SO::P*)out, L);
         return hipGetLastError();
     }
-    return launch_layer_ct<SI, SO, SL, kLayerCT>(c, U, W, in, out, 0, L / kLayerCT, s);
+    const SiteMap sm = make_site_map_rows(c->g, 12.0 * L * sizeof(typename SI::P) + 36.0 * sizeof(typename SL::P), 4);
+    dim3 block(64, L), grid(sm.nblk);
+    k_layer<SI, SO, SL, 1><<<grid, block, 0, s>>>(c->g, sm, U, W, (const typename SI::P*)in, (typename SO::P*)out, 0, L);
+    return hipGetLastError();
 }
 
+// One FP32 layer.
 template <class SI, class SO>
 hipError_t launch_layer(const wd_ctx* c, const float2* W, const void* in, void* out, int L, hipStream_t s) {
-    return launch_layer<SI, SO, StF32>(c, c->U32, W, in, out, L, s);
+    const SiteMap sm = make_site_map_rows(c->g, 12.0 * L * sizeof(typename SI::P) + 72.0 * 8, 4);
+    const typename SI::P* zi = (const typename SI::P*)in;
+    typename SO::P* zo = (typename SO::P*)out;
+    if (L >= 3) {
+        // a workgroup takes all columns of its tile (the links staged once) unless the tiles alone
+        // leave CUs without work: then groups of four columns
+        const int cpg = sm.nblk < 256 ? 4 : 4 * ((L + 3) / 4);
+        k_layer_f32<SI, SO, true><<<dim3(sm.nblk, (L + cpg - 1) / cpg), dim3(64, 4), 0, s>>>(c->g, sm, c->U32, W, zi,
+                                                                                          zo, L, cpg);
+    } else {
+        k_layer_f32<SI, SO, false><<<sm.nblk, dim3(64, L), 0, s>>>(c->g, sm, c->U32, W, zi, zo, L, L);
+    }
+    return hipGetLastError();
 }
 
 constexpr int kWgBlocks = 64;
@@ -560,7 +639,7 @@ struct LearnWs {
 int learn_ws(wd_ctx* c, LearnWs& w) {
     // the learned workspace lives in the low-precision Jacobi buffers (3 blocks) plus a
     // dedicated set for training
-    const size_t blk = (size_t)12 * c->g.V * c->max_L;
+    const size_t blk = lowp_tiles(c->g) * 768 * c->max_L;
     if (!c->learn_mem) {
         const size_t bytes = 2 * blk * sizeof(float2) + (size_t)kWgBlocks * WD_MAX_L * 16 * sizeof(double2) +
                              3 * kNL * kND * 16 * sizeof(double2) + kND * 16 * sizeof(float2) +
@@ -620,14 +699,24 @@ hipError_t launch_learned(wd_ctx* c, const double2* R, double2* Z, int L, Prec p
     }
     float2* t0 = (float2*)c->lp[0];
     float2* t1 = (float2*)c->lp[1];
-    hipError_t e = launch_layer<StF64, StF32>(c, c->theta, R, t0, L, s);
-    if (e == hipSuccess) e = launch_layer<StF32, StF32>(c, c->theta + kND * 16, t0, t1, L, s);
-    if (e == hipSuccess) e = launch_layer<StF32, StF64>(c, c->theta + 2 * kND * 16, t1, Z, L, s);
+    hipError_t e = launch_layer<StF64, StF32P>(c, c->theta, R, t0, L, s);
+    if (e == hipSuccess) e = launch_layer<StF32P, StF32P>(c, c->theta + kND * 16, t0, t1, L, s);
+    if (e == hipSuccess) e = launch_layer<StF32P, StF64>(c, c->theta + 2 * kND * 16, t1, Z, L, s);
     return e;
 }
 
-// Loss of one batch into w.loss and dl/d(conj y) (FP32) into w.g[0], from the forward output
-// w.z[2].  kind WD_LOSS_ERROR: ||y - e||^2 / ||e||^2; WD_LOSS_RESIDUAL: ||A y - r||^2 / ||r||^2,
+// The forward pass of one batch: z0 = R (FP64) -> z1 -> z2 in FP32, then y, in FP32 (w.z[2]) for
+// the error loss and widened to FP64 (ws[9]) for the residual loss, which applies A to it.
+hipError_t batch_forward(wd_ctx* c, LearnWs& w, const double2* Rb, int L, int kind, hipStream_t s) {
+    hipError_t e = launch_layer<StF64, StF32P>(c, c->theta, Rb, w.z[0], L, s);
+    if (e == hipSuccess) e = launch_layer<StF32P, StF32P>(c, c->theta + kND * 16, w.z[0], w.z[1], L, s);
+    if (e != hipSuccess) return e;
+    if (kind == WD_LOSS_ERROR) return launch_layer<StF32P, StF32P>(c, c->theta + 2 * kND * 16, w.z[1], w.z[2], L, s);
+    return launch_layer<StF32P, StF64>(c, c->theta + 2 * kND * 16, w.z[1], c->ws[9], L, s);
+}
+
+// Loss of one batch into w.loss and dl/d(conj y) (FP32) into w.g[0], from the forward output.
+// kind WD_LOSS_ERROR: ||y - e||^2 / ||e||^2; WD_LOSS_RESIDUAL: ||A y - r||^2 / ||r||^2,
 // whose gradient needs two FP64 applications of A (scratch: the solver blocks T1 and the Jacobi
 // temporary, ws[9] and ws[10], idle while training).
 hipError_t batch_loss(wd_ctx* c, LearnWs& w, const double2* Rb, const double2* Eb, int L, int kind, hipStream_t s) {
@@ -636,7 +725,7 @@ hipError_t batch_loss(wd_ctx* c, LearnWs& w, const double2* Rb, const double2* E
     if (kind == WD_LOSS_ERROR) {
         hipError_t e = launch_colnorms(Eb, ncol, L, c->partial, gram_blocks(ncol), w.en2, s);
         if (e != hipSuccess) return e;
-        k_loss<<<lblocks, kGB, 0, s>>>(w.z[2], Eb, w.en2, ncol, L, w.g[0], w.lpart);
+        k_loss<<<lblocks, kGB, 0, s>>>(c->g, w.z[2], Eb, w.en2, ncol, L, w.g[0], w.lpart);
         k_reduce_loss<<<1, kGB, 0, s>>>(w.lpart, lblocks, L, w.loss);
         return hipGetLastError();
     }
@@ -644,12 +733,11 @@ hipError_t batch_loss(wd_ctx* c, LearnWs& w, const double2* Rb, const double2* E
     double2* t2 = c->ws[10];
     hipError_t e = launch_colnorms(Rb, ncol, L, c->partial, gram_blocks(ncol), w.en2, s);
     if (e != hipSuccess) return e;
-    k_to_f64<<<nblk(n, 256), 256, 0, s>>>(w.z[2], t1, n);
     if ((e = launch_apply_A(c, t1, t2, L, s)) != hipSuccess) return e;      // A y
     k_res_loss<<<lblocks, kGB, 0, s>>>(t2, Rb, w.en2, ncol, L, t1, w.lpart, c->g.vt & kVecTiled);  // gamma5 (A y - r) / ...
     k_reduce_loss<<<1, kGB, 0, s>>>(w.lpart, lblocks, L, w.loss);
     if ((e = launch_apply_A(c, t1, t2, L, s)) != hipSuccess) return e;      // A gamma5 (A y - r)
-    k_gamma5_to_f32<<<nblk(n, 256), 256, 0, s>>>(t2, w.g[0], ncol, n, c->g.vt & kVecTiled);
+    k_gamma5_to_f32<<<nblk(n, 256), 256, 0, s>>>(c->g, t2, w.g[0], n);
     return hipGetLastError();
 }
 
@@ -768,11 +856,7 @@ int wd_learned_train(wd_ctx* c, const void* Rp, const void* Ep, int n_pairs, int
         const int b = step % nbatch;
         const double2* Rb = (const double2*)Rp + (size_t)b * L * ncol;
         const double2* Eb = Ep ? (const double2*)Ep + (size_t)b * L * ncol : nullptr;
-        // forward: z0 = R (FP64) -> z1 -> z2 -> y (FP32, kept for the loss)
-        if (launch_layer<StF64, StF32>(c, c->theta, Rb, w.z[0], L, s) != hipSuccess) return WD_EHIP;
-        if (launch_layer<StF32, StF32>(c, c->theta + kND * 16, w.z[0], w.z[1], L, s) != hipSuccess) return WD_EHIP;
-        if (launch_layer<StF32, StF32>(c, c->theta + 2 * kND * 16, w.z[1], w.z[2], L, s) != hipSuccess)
-            return WD_EHIP;
+        if (batch_forward(c, w, Rb, L, loss_kind, s) != hipSuccess) return WD_EHIP;
         // loss and dl/d(conj y)
         if (batch_loss(c, w, Rb, Eb, L, loss_kind, s) != hipSuccess) return WD_EHIP;
         // backward through layers 2, 1, 0
@@ -783,12 +867,12 @@ int wd_learned_train(wd_ctx* c, const void* Rp, const void* Ep, int n_pairs, int
                 if (l == 0)
                     k_wgrad<StF64><<<grid, kGB, 0, s>>>(c->g, c->U32, Rb, w.g[gi], d, w.gpart);
                 else
-                    k_wgrad<StF32><<<grid, kGB, 0, s>>>(c->g, c->U32, w.z[l - 1], w.g[gi], d, w.gpart);
+                    k_wgrad<StF32P><<<grid, kGB, 0, s>>>(c->g, c->U32, w.z[l - 1], w.g[gi], d, w.gpart);
                 k_reduce16<<<1, kGB, 0, s>>>(w.gpart, kWgBlocks * L, w.G + (l * kND + d) * 16);
             }
             if (l > 0) {
                 k_adjoint_weights<<<1, 192, 0, s>>>(c->theta + l * kND * 16, w.Wa);
-                if (launch_layer<StF32, StF32>(c, w.Wa, w.g[gi], w.g[1 - gi], L, s) != hipSuccess) return WD_EHIP;
+                if (launch_layer<StF32P, StF32P>(c, w.Wa, w.g[gi], w.g[1 - gi], L, s) != hipSuccess) return WD_EHIP;
                 gi = 1 - gi;
             }
         }
@@ -820,9 +904,7 @@ int wd_learned_grad(wd_ctx* c, const void* R, const void* E, int L, int loss_kin
     hipStream_t s = c->stream;
     const double2* Rb = (const double2*)R;
     const double2* Eb = (const double2*)E;
-    if (launch_layer<StF64, StF32>(c, c->theta, Rb, w.z[0], L, s) != hipSuccess) return WD_EHIP;
-    if (launch_layer<StF32, StF32>(c, c->theta + kND * 16, w.z[0], w.z[1], L, s) != hipSuccess) return WD_EHIP;
-    if (launch_layer<StF32, StF32>(c, c->theta + 2 * kND * 16, w.z[1], w.z[2], L, s) != hipSuccess) return WD_EHIP;
+    if (batch_forward(c, w, Rb, L, loss_kind, s) != hipSuccess) return WD_EHIP;
     if (batch_loss(c, w, Rb, Eb, L, loss_kind, s) != hipSuccess) return WD_EHIP;
     int gi = 0;
     for (int l = kNL - 1; l >= 0; --l) {
@@ -831,12 +913,12 @@ int wd_learned_grad(wd_ctx* c, const void* R, const void* E, int L, int loss_kin
             if (l == 0)
                 k_wgrad<StF64><<<grid, kGB, 0, s>>>(c->g, c->U32, Rb, w.g[gi], d, w.gpart);
             else
-                k_wgrad<StF32><<<grid, kGB, 0, s>>>(c->g, c->U32, w.z[l - 1], w.g[gi], d, w.gpart);
+                k_wgrad<StF32P><<<grid, kGB, 0, s>>>(c->g, c->U32, w.z[l - 1], w.g[gi], d, w.gpart);
             k_reduce16<<<1, kGB, 0, s>>>(w.gpart, kWgBlocks * L, w.G + (l * kND + d) * 16);
         }
         if (l > 0) {
             k_adjoint_weights<<<1, 192, 0, s>>>(c->theta + l * kND * 16, w.Wa);
-            if (launch_layer<StF32, StF32>(c, w.Wa, w.g[gi], w.g[1 - gi], L, s) != hipSuccess) return WD_EHIP;
+            if (launch_layer<StF32P, StF32P>(c, w.Wa, w.g[gi], w.g[1 - gi], L, s) != hipSuccess) return WD_EHIP;
             gi = 1 - gi;
         }
     }

@@ -245,6 +245,28 @@ __global__ void k_convert(const double2* __restrict__ src, typename S::P* __rest
     S::st(dst, i, cx<typename S::R>{(typename S::R)(scale * v.x), (typename S::R)(scale * v.y)});
 }
 
+// FP64 block vector (layout of g) -> library block in storage S, one thread per source element
+template <class S>
+__global__ void k_to_lowp(const double2* __restrict__ src, typename S::P* __restrict__ dst, const Geom g, size_t n) {
+    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const double2 v = src[i];
+    const size_t N = (size_t)12 * g.V, col = i / N;
+    int k, site;
+    row_of(g, i - col * N, k, site);
+    S::stb(dst + col * Vec<S>::col(g) + Vec<S>::at(64, k), Vec<S>::off(g, site),
+           cx<typename S::R>{(typename S::R)v.x, (typename S::R)v.y});
+}
+
+__global__ void k_links_f32(const double2* __restrict__ src, float* __restrict__ dst, size_t V) {
+    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= 36 * V) return;
+    const double2 v = src[i];
+    const size_t p = i / V, s = i - p * V;
+    dst[2 * p * V + s] = (float)v.x;
+    dst[(2 * p + 1) * V + s] = (float)v.y;
+}
+
 __global__ void k_point_form(const double2* __restrict__ T, double2* __restrict__ Tp, size_t V) {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= 36 * V) return;
@@ -290,8 +312,20 @@ hipError_t launch_point_form(const double2* T, double2* Tp, size_t V, hipStream_
     return hipGetLastError();
 }
 
-hipError_t launch_to_lowp(const double2* src, void* dst, Prec p, size_t n, hipStream_t s) {
-    return launch_convert(src, dst, p, 1.0, n, s);
+hipError_t launch_to_lowp(const double2* src, void* dst, Prec p, const Geom& g, int L, hipStream_t s) {
+    const size_t n = (size_t)12 * g.V * L;
+    if (p == Prec::F32)
+        k_to_lowp<StF32P><<<nblk(n, 256), 256, 0, s>>>(src, (float2*)dst, g, n);
+    else if (p == Prec::BF16)
+        k_to_lowp<StBF16><<<nblk(n, 256), 256, 0, s>>>(src, (uint32_t*)dst, g, n);
+    else
+        return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+hipError_t launch_links_f32(const double2* src, float* dst, size_t V, hipStream_t s) {
+    k_links_f32<<<nblk(36 * V, 256), 256, 0, s>>>(src, dst, V);
+    return hipGetLastError();
 }
 
 }  // namespace wd

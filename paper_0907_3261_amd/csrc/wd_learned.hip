@@ -22,57 +22,6 @@ namespace {
 
 constexpr int kNL = WD_LEARNED_LAYERS, kND = WD_LEARNED_DIRS;
 
-// S_d psi for one column at site s: returns 12 complex (index 3*spin + colour).  V:
-// sites (the links' plane stride); KS, ob: the plane stride of the block vector
-// and the byte offset of nb (s for d = 0) in it.
-template <class SZ>
-__device__ __forceinline__ void shifted(const float* __restrict__ U, const typename SZ::P* __restrict__ Z, size_t V,
-                                        size_t KS, int d, int s, int nb, uint32_t ob, cx<float> (&q)[12]) {
-    cx<typename SZ::R> z[12];
-    Vec<SZ>::template load<false>(z, Z, KS, 0, ob);
-    cx<float> p[12];
-#pragma unroll
-    for (int k = 0; k < 12; ++k) p[k] = {(float)z[k].re, (float)z[k].im};
-    if (d == 0) {
-#pragma unroll
-        for (int k = 0; k < 12; ++k) q[k] = p[k];
-        return;
-    }
-    const int mu = (d - 1) >> 1;
-    const bool fwd = (d & 1) != 0;
-    const int ls = fwd ? s : nb;
-    cx<float> u[9];
-#pragma unroll
-    for (int k = 0; k < 9; ++k) {
-        const float* ur = U + (size_t)(mu * 9 + k) * 2 * V;
-        u[k] = {ur[ls], ur[V + ls]};
-    }
-#pragma unroll
-    for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            cx<float> r = {0.f, 0.f};
-#pragma unroll
-            for (int b = 0; b < 3; ++b) {
-                if (fwd)
-                    cfma(r, u[a * 3 + b], p[3 * sp + b]);
-                else
-                    cfmac(r, u[b * 3 + a], p[3 * sp + b]);
-            }
-            q[3 * sp + a] = r;
-        }
-}
-
-__device__ __forceinline__ int neighbour(const Geom& g, int s, int d) {
-    if (d == 0) return s;
-    const int mu = (d - 1) >> 1;
-    const int step = (d & 1) ? 1 : -1;
-    int c[4] = {s % g.lx, (s / g.lx) % g.ly, (s / g.sxy) % g.lz, s / g.sxyz};
-    const int ext[4] = {g.lx, g.ly, g.lz, g.lt};
-    c[mu] = (c[mu] + step + ext[mu]) % ext[mu];
-    return c[0] + g.lx * (c[1] + g.ly * (c[2] + g.lz * c[3]));
-}
-
 // Operands of one term W_d (U or U^dag or 1) psi(nb): the link and the CT input spinors.
 template <class R, int CT>
 struct Term {
@@ -204,61 +153,122 @@ __global__ void k_adjoint_weights(const float2* __restrict__ W, float2* __restri
 
 constexpr int kGB = 256;  // threads of the reduction kernels
 
-// partial[(col * gridDim.x + block) * 16 + e] = sum over this block's sites of
-//   2 sum_a g[3 s + a] conj((S_d z)[3 t + a]),  e = 4 s + t
+// Weight gradient of one layer, all nine directions in one pass:
+//   partial[(d * gridDim.x + block) * 16 + e] = sum over the block's sites and columns of
+//   2 sum_a g[3 s + a] conj((S_d z)[3 t + a]),  e = 4 s + t,
+// the colour sums in FP32, the site sums in FP64.  A workgroup takes (tile, column) pairs of 64
+// sites in turn; its wave d - 1 forms the columns t = 2 h and 2 h + 1 (h = blockIdx.y) of hop
+// direction d, and one of the sixteen elements of the self term, so that no wave keeps more than
+// nine complex sums and six waves fit a SIMD.  The gradient's spinor and the neighbours' come from
+// memory once and from the caches after that; a launch per direction read both again for each.
+// What bounds it now is the L1: 30 loads a wave and pair, of which the 18 of the link are 256 B
+// each.  16^3 x 32, L = 12, one layer with its reductions: 9 x (60 + 13) us by direction, 391 us
+// (FP64 input 525).
+constexpr int kWgBlocks = 256;  // workgroups per h
 template <class SZ>
-__global__ void __launch_bounds__(kGB) k_wgrad(const Geom g, const float* __restrict__ U,
-                                               const typename SZ::P* __restrict__ Z, const float2* __restrict__ Gr,
-                                               int d, double2* __restrict__ partial) {
-    __shared__ double sh[kGB / 64][32];
-    const size_t V = g.V, KS = Vec<SZ>::plane(g);
-    const int col = blockIdx.y;
-    const typename SZ::P* zc = Z + (size_t)col * Vec<SZ>::col(g);
-    const float2* gc = Gr + (size_t)col * Vec<StF32P>::col(g);
-    double acc[32];
+__global__ void __launch_bounds__(512, 6) k_wgrad(const Geom g, const float* __restrict__ U,
+                                                const typename SZ::P* __restrict__ Z, const float2* __restrict__ Gr,
+                                                const int L, double2* __restrict__ partial) {
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int mu = wv >> 1, half = blockIdx.y;
+    const bool fwd = (wv & 1) == 0;
+    const float usgn = fwd ? 1.f : -1.f;
+    const uint32_t V = g.V;
+    const uint32_t str = mu == 0 ? 1u : mu == 1 ? (uint32_t)g.lx : mu == 2 ? (uint32_t)g.sxy : (uint32_t)g.sxyz;
+    const uint32_t ext = mu == 0 ? g.lx : mu == 1 ? g.ly : mu == 2 ? g.lz : g.lt;
+    const size_t KS = Vec<SZ>::plane(g);
+    const int self = 2 * wv + half, es = self >> 2, et = self & 3;  // this wave's element of the self term
+    double acc[8][2], self_re = 0.0, self_im = 0.0;  // acc[4 t' + sp], t = 2 half + t'
 #pragma unroll
-    for (int e = 0; e < 32; ++e) acc[e] = 0.0;
-    for (int s = blockIdx.x * kGB + threadIdx.x; s < g.V; s += gridDim.x * kGB) {
-        cx<float> q[12], gv[12];
-        const int nb = neighbour(g, s, d);
-        shifted<SZ>(U, zc, V, KS, d, s, nb, Vec<SZ>::off(g, nb), q);
-        const uint32_t og = Vec<StF32P>::off(g, s);
-        Vec<StF32P>::load<false>(gv, gc, 64, 0, og);
+    for (int e = 0; e < 8; ++e) acc[e][0] = acc[e][1] = 0.0;
+    const int nt = (int)((V + 63) / 64);
+    // tile b of a column goes to workgroup b % gridDim.x of every column: neighbouring tiles run
+    // at the same time, and a workgroup's tiles stay on its XCD
+    for (int col = 0; col < L; ++col) {
+        const typename SZ::P* zc = Z + (size_t)col * Vec<SZ>::col(g);
+        const float2* gc = Gr + (size_t)col * Vec<StF32P>::col(g);
+        for (int b = blockIdx.x; b < nt; b += gridDim.x) {
+            const uint32_t s = (uint32_t)b * 64 + lane;
+            if (s >= V) continue;
+            const uint32_t co = (s / str) % ext;
+            const uint32_t nb = fwd ? (co + 1 == ext ? s - (ext - 1) * str : s + str)
+                                    : (co == 0 ? s + (ext - 1) * str : s - str);
+            const uint32_t on = Vec<SZ>::off(g, nb), oz = Vec<SZ>::off(g, s), og = Vec<StF32P>::off(g, s);
+            cx<float> gv[12], u[9], gs[3];
+            cx<typename SZ::R> z[6], zs[3];
 #pragma unroll
-        for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                cx<float> r = {0.f, 0.f};
-#pragma unroll
-                for (int a = 0; a < 3; ++a) cfma(r, gv[3 * sp + a], conj(q[3 * t + a]));
-                acc[2 * (sp * 4 + t)] += 2.0 * r.re;
-                acc[2 * (sp * 4 + t) + 1] += 2.0 * r.im;
+            for (int k = 0; k < 6; k += Vec<SZ>::G) {
+                if constexpr (Vec<SZ>::G == 1)
+                    z[k] = SZ::ldb(zc + (size_t)(6 * half + k) * KS, on);
+                else
+                    Vec<SZ>::template load_group<false>(&z[k], zc, 6 * half + k, on);
             }
-    }
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+            Vec<StF32P>::load<false>(gv, gc, 64, 0, og);
+            // U (forward) or U^dag (backward)
+            const uint32_t ls = fwd ? s : nb;
 #pragma unroll
-    for (int e = 0; e < 32; ++e) {
-        double v = acc[e];
+            for (int k = 0; k < 9; ++k) {
+                const float* ur = U + (size_t)(mu * 9 + (fwd ? k : k % 3 * 3 + k / 3)) * 2 * V;
+                const float* ui = ur + V;
+                u[k] = {ur[ls], usgn * ui[ls]};
+            }
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                gs[a] = StF32::ldb(gc + Vec<StF32P>::at(64, 3 * es + a), og);
+                zs[a] = SZ::ldb(zc + Vec<SZ>::at(KS, 3 * et + a), oz);
+            }
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                cx<float> q[3];
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    cx<float> r = {0.f, 0.f};
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        const cx<float> p = {(float)z[3 * t + c].re, (float)z[3 * t + c].im};
+                        cfma(r, u[a * 3 + c], p);
+                    }
+                    q[a] = r;
+                }
+#pragma unroll
+                for (int sp = 0; sp < 4; ++sp) {
+                    cx<float> r = {0.f, 0.f};
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) cfma(r, gv[3 * sp + a], conj(q[a]));
+                    acc[4 * t + sp][0] += 2.0 * r.re;
+                    acc[4 * t + sp][1] += 2.0 * r.im;
+                }
+            }
+            cx<float> r = {0.f, 0.f};
+#pragma unroll
+            for (int a = 0; a < 3; ++a) cfma(r, gs[a], conj(cx<float>{(float)zs[a].re, (float)zs[a].im}));
+            self_re += 2.0 * r.re;
+            self_im += 2.0 * r.im;
+        }
+    }
+    const auto wave_total = [](double v) {
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-        if (lane == 0) sh[w][e] = v;
+        return v;
+    };
+    const size_t np = gridDim.x;
+    double2* pd = partial + ((size_t)(1 + wv) * np + blockIdx.x) * 16;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const double re = wave_total(acc[e][0]), im = wave_total(acc[e][1]);
+        if (lane == 0) pd[4 * (e & 3) + 2 * half + (e >> 2)] = make_double2(re, im);
     }
-    __syncthreads();
-    if (threadIdx.x < 16) {
-        double re = 0.0, im = 0.0;
-        for (int q = 0; q < kGB / 64; ++q) {
-            re += sh[q][2 * threadIdx.x];
-            im += sh[q][2 * threadIdx.x + 1];
-        }
-        partial[((size_t)col * gridDim.x + blockIdx.x) * 16 + threadIdx.x] = make_double2(re, im);
-    }
+    self_re = wave_total(self_re);
+    self_im = wave_total(self_im);
+    if (lane == 0) partial[(size_t)blockIdx.x * 16 + self] = make_double2(self_re, self_im);
 }
 
-// out[e] = sum_p partial[p * 16 + e] (fixed order), e < 16
+// out[16 d + e] = sum_p partial[(d * np + p) * 16 + e] (fixed order), e < 16, d = blockIdx.x
 __global__ void __launch_bounds__(kGB) k_reduce16(const double2* __restrict__ partial, int np,
                                                   double2* __restrict__ out) {
     __shared__ double2 sh[kGB];
     const int e = threadIdx.x & 15, gq = threadIdx.x >> 4;  // 16 groups
+    partial += (size_t)blockIdx.x * np * 16;
     double2 s = make_double2(0.0, 0.0);
     for (int p = gq; p < np; p += kGB / 16) {
         const double2 v = partial[(size_t)p * 16 + e];
@@ -273,7 +283,7 @@ __global__ void __launch_bounds__(kGB) k_reduce16(const double2* __restrict__ pa
             a.x += sh[q * 16 + threadIdx.x].x;
             a.y += sh[q * 16 + threadIdx.x].y;
         }
-        out[threadIdx.x] = a;
+        out[(size_t)blockIdx.x * 16 + threadIdx.x] = a;
     }
 }
 
@@ -621,8 +631,6 @@ hipError_t launch_layer(const wd_ctx* c, const float2* W, const void* in, void* 
     return hipGetLastError();
 }
 
-constexpr int kWgBlocks = 64;
-
 struct LearnWs {
     float2* z[3];       // FP32 activations z1, z2, z3 (z0 is the FP64 input)
     float2* g[2];       // FP32 gradient ping-pong
@@ -641,7 +649,7 @@ int learn_ws(wd_ctx* c, LearnWs& w) {
     // dedicated set for training
     const size_t blk = lowp_tiles(c->g) * 768 * c->max_L;
     if (!c->learn_mem) {
-        const size_t bytes = 2 * blk * sizeof(float2) + (size_t)kWgBlocks * WD_MAX_L * 16 * sizeof(double2) +
+        const size_t bytes = 2 * blk * sizeof(float2) + (size_t)kND * kWgBlocks * 16 * sizeof(double2) +
                              3 * kNL * kND * 16 * sizeof(double2) + kND * 16 * sizeof(float2) +
                              4096 * sizeof(double) + WD_MAX_L * sizeof(double) + 64;
         if (hipMalloc(&c->learn_mem, bytes) != hipSuccess) {
@@ -664,7 +672,7 @@ int learn_ws(wd_ctx* c, LearnWs& w) {
     w.g[1] = (float2*)p;
     p += blk * sizeof(float2);
     w.gpart = (double2*)p;
-    p += (size_t)kWgBlocks * WD_MAX_L * 16 * sizeof(double2);
+    p += (size_t)kND * kWgBlocks * 16 * sizeof(double2);
     w.G = (double2*)p;
     p += kNL * kND * 16 * sizeof(double2);
     w.m = (double2*)p;
@@ -738,6 +746,27 @@ hipError_t batch_loss(wd_ctx* c, LearnWs& w, const double2* Rb, const double2* E
     k_reduce_loss<<<1, kGB, 0, s>>>(w.lpart, lblocks, L, w.loss);
     if ((e = launch_apply_A(c, t1, t2, L, s)) != hipSuccess) return e;      // A gamma5 (A y - r)
     k_gamma5_to_f32<<<nblk(n, 256), 256, 0, s>>>(c->g, t2, w.g[0], n);
+    return hipGetLastError();
+}
+
+// Weight gradients of layers 2, 1, 0 into w.G, from dl/d(conj y) in w.g[0] and the activations.
+hipError_t batch_backward(wd_ctx* c, LearnWs& w, const double2* Rb, int L, hipStream_t s) {
+    const int tiles = (int)lowp_tiles(c->g);
+    const int nb = tiles < kWgBlocks ? tiles : kWgBlocks;
+    int gi = 0;
+    for (int l = kNL - 1; l >= 0; --l) {
+        if (l == 0)
+            k_wgrad<StF64><<<dim3(nb, 2), 512, 0, s>>>(c->g, c->U32, Rb, w.g[gi], L, w.gpart);
+        else
+            k_wgrad<StF32P><<<dim3(nb, 2), 512, 0, s>>>(c->g, c->U32, w.z[l - 1], w.g[gi], L, w.gpart);
+        k_reduce16<<<kND, kGB, 0, s>>>(w.gpart, nb, w.G + l * kND * 16);
+        if (l > 0) {
+            k_adjoint_weights<<<1, 192, 0, s>>>(c->theta + l * kND * 16, w.Wa);
+            const hipError_t e = launch_layer<StF32P, StF32P>(c, w.Wa, w.g[gi], w.g[1 - gi], L, s);
+            if (e != hipSuccess) return e;
+            gi = 1 - gi;
+        }
+    }
     return hipGetLastError();
 }
 
@@ -859,24 +888,7 @@ int wd_learned_train(wd_ctx* c, const void* Rp, const void* Ep, int n_pairs, int
         if (batch_forward(c, w, Rb, L, loss_kind, s) != hipSuccess) return WD_EHIP;
         // loss and dl/d(conj y)
         if (batch_loss(c, w, Rb, Eb, L, loss_kind, s) != hipSuccess) return WD_EHIP;
-        // backward through layers 2, 1, 0
-        int gi = 0;
-        for (int l = kNL - 1; l >= 0; --l) {
-            for (int d = 0; d < kND; ++d) {
-                dim3 grid(kWgBlocks, L);
-                if (l == 0)
-                    k_wgrad<StF64><<<grid, kGB, 0, s>>>(c->g, c->U32, Rb, w.g[gi], d, w.gpart);
-                else
-                    k_wgrad<StF32P><<<grid, kGB, 0, s>>>(c->g, c->U32, w.z[l - 1], w.g[gi], d, w.gpart);
-                k_reduce16<<<1, kGB, 0, s>>>(w.gpart, kWgBlocks * L, w.G + (l * kND + d) * 16);
-            }
-            if (l > 0) {
-                k_adjoint_weights<<<1, 192, 0, s>>>(c->theta + l * kND * 16, w.Wa);
-                if (launch_layer<StF32P, StF32P>(c, w.Wa, w.g[gi], w.g[1 - gi], L, s) != hipSuccess) return WD_EHIP;
-                gi = 1 - gi;
-            }
-        }
-        if (hipGetLastError() != hipSuccess) return WD_EHIP;
+        if (batch_backward(c, w, Rb, L, s) != hipSuccess) return WD_EHIP;
         k_adam<<<nblk(nparam, 256), 256, 0, s>>>(c->theta, w.G, w.m, w.v, nparam, step + 1, lr, 0.9, 0.999, 1e-8);
         if (loss_hist) {
             double lv = 0.0;
@@ -906,23 +918,7 @@ int wd_learned_grad(wd_ctx* c, const void* R, const void* E, int L, int loss_kin
     const double2* Eb = (const double2*)E;
     if (batch_forward(c, w, Rb, L, loss_kind, s) != hipSuccess) return WD_EHIP;
     if (batch_loss(c, w, Rb, Eb, L, loss_kind, s) != hipSuccess) return WD_EHIP;
-    int gi = 0;
-    for (int l = kNL - 1; l >= 0; --l) {
-        for (int d = 0; d < kND; ++d) {
-            dim3 grid(kWgBlocks, L);
-            if (l == 0)
-                k_wgrad<StF64><<<grid, kGB, 0, s>>>(c->g, c->U32, Rb, w.g[gi], d, w.gpart);
-            else
-                k_wgrad<StF32P><<<grid, kGB, 0, s>>>(c->g, c->U32, w.z[l - 1], w.g[gi], d, w.gpart);
-            k_reduce16<<<1, kGB, 0, s>>>(w.gpart, kWgBlocks * L, w.G + (l * kND + d) * 16);
-        }
-        if (l > 0) {
-            k_adjoint_weights<<<1, 192, 0, s>>>(c->theta + l * kND * 16, w.Wa);
-            if (launch_layer<StF32P, StF32P>(c, w.Wa, w.g[gi], w.g[1 - gi], L, s) != hipSuccess) return WD_EHIP;
-            gi = 1 - gi;
-        }
-    }
-    if (hipGetLastError() != hipSuccess) return WD_EHIP;
+    if (batch_backward(c, w, Rb, L, s) != hipSuccess) return WD_EHIP;
     if (hipMemcpyAsync(loss, w.loss, sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess) return WD_EHIP;
     if (hipMemcpyAsync(G_host, w.G, kNL * kND * 16 * sizeof(double2), hipMemcpyDeviceToHost, s) != hipSuccess)
         return WD_EHIP;

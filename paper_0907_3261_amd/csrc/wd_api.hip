@@ -193,7 +193,7 @@ int wd_create(wd_ctx** out, const int dims[4], int bc_t, int max_L, void* hip_st
         r = r ? r : dev_alloc(&c->f.Tc[p], clov * psz[p]);
     }
     for (auto& w : c->ws) r = r ? r : dev_alloc((void**)&w, block_elems(c, max_L) * 16);
-    r = r ? r : dev_alloc((void**)&c->partial, (size_t)512 * partial_stride() * 16);
+    r = r ? r : dev_alloc((void**)&c->partial, partial_pairs() * 16);
     r = r ? r : dev_alloc((void**)&c->small, kSmallPairs * 16);
     r = r ? r : dev_alloc((void**)&c->U32, links * 8);
     r = r ? r : dev_alloc((void**)&c->theta, (size_t)WD_LEARNED_LAYERS * WD_LEARNED_DIRS * 16 * 8);

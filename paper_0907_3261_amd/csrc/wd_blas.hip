@@ -198,222 +198,187 @@ __global__ void __launch_bounds__(kWG) k_colnorms(const double2* __restrict__ R,
 }
 
 // ---------------------------------------------------------------------------
-// Single-workgroup reduction of partials and L x L solves
+// Reduction of partials and L x L solves
 // ---------------------------------------------------------------------------
-constexpr int kRT = 1024;  // threads of the reduce/solve kernels
-
-// Reduce E = L*L tile entries (if tile) plus n_extra extras over nb partial
-// blocks, in a fixed order, into out[0..E).
-__device__ void reduce_partials(const double2* __restrict__ partial, int nb, int L, bool tile, int n_extra,
-                                double2* out, double2* scratch /* kRT entries */) {
-    const int nt = tile ? L * L : 0;
-    const int E = nt + n_extra;
-    const int G = kRT / E;  // >= 3 since E <= 272
-    const int t = threadIdx.x;
-    const int g = t / E, e = t % E;
+// Row b of every partial block (b < 16: row b of the tile, 16: the extras) summed over the nb
+// blocks in a fixed order: out[b * stride + e], e < n.  One workgroup per row, sixteen threads per
+// entry: one workgroup for all rows took 35 us for 384 blocks at L = 12, most of each
+// alpha and gamma solve on small lattices; this takes 5.
+__global__ void __launch_bounds__(kWG) k_reduce_rows(const double2* __restrict__ partial, int nb, int row0,
+                                                     double2* __restrict__ out, int stride, int n) {
+    __shared__ double2 sh[kWG];
+    const int e = threadIdx.x & 15, q = threadIdx.x >> 4;
+    const double2* p = partial + (size_t)(row0 + blockIdx.x) * 16 + e;
     double2 s = make_double2(0.0, 0.0);
-    if (g < G) {
-        const int idx = (e < nt) ? (e / L) * 16 + (e % L) : 256 + (e - nt);
-        for (int b = g; b < nb; b += G) {
-            const double2 v = partial[(size_t)b * kPStride + idx];
-            s.x += v.x;
-            s.y += v.y;
-        }
-        scratch[g * E + e] = s;
+#pragma unroll 8
+    for (int b = q; b < nb; b += kWG / 16) {
+        const double2 v = p[(size_t)b * kPStride];
+        s.x += v.x;
+        s.y += v.y;
     }
+    sh[threadIdx.x] = s;
     __syncthreads();
-    if (t < E) {
-        double2 a = scratch[t];
-        for (int q = 1; q < G; ++q) {
-            a.x += scratch[q * E + t].x;
-            a.y += scratch[q * E + t].y;
+    if ((int)threadIdx.x < n && threadIdx.x < 16) {
+        double2 t = sh[threadIdx.x];
+#pragma unroll
+        for (int g = 1; g < kWG / 16; ++g) {
+            t.x += sh[g * 16 + threadIdx.x].x;
+            t.y += sh[g * 16 + threadIdx.x].y;
         }
-        out[t] = a;
+        out[(size_t)blockIdx.x * stride + threadIdx.x] = t;
     }
-    __syncthreads();
 }
 
 __device__ __forceinline__ bool finite2(double2 v) { return isfinite(v.x) && isfinite(v.y); }
 __device__ __forceinline__ double cabs2(cx<double> a) { return a.re * a.re + a.im * a.im; }
 
-struct SolveShared {
-    double2 scratch[kRT];
-    double2 red[16 * 16 + 16];
-    double2 M[256], RHS[256], sol[256];
-    double2 aug[16 * 32];
-    double fac[2 * 16];
-    double scale;
-    double pmin, pmax;  // smallest and largest pivot modulus of the last factorisation
-    int piv;
-    int flag;
-};
+// value of lane l (uniform) in every lane
+__device__ __forceinline__ double lane_of(double v, int l) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, l), hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), l);
+    return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
+}
+__device__ __forceinline__ cx<double> lane_of(cx<double> v, int l) { return {lane_of(v.re, l), lane_of(v.im, l)}; }
 
-// Solve M Z = RHS (L x L row-major in shared memory) by LU with partial
-// pivoting into sm.sol (row-major).  Returns false (uniformly across the
-// workgroup) on a pivot below 1e-14 max|M| or a non-finite entry.  The
-// ratio sm.pmax / sm.pmin of the pivot moduli is a cheap estimate of the
-// condition of M (a lower bound of it for this pivot order).
-__device__ bool lu_solve_shared(SolveShared& sm, int L) {
+// Solve M Z = RHS (L <= LM) by LU with partial pivoting in one wavefront: lane c < L holds column
+// c of M in a[0 .. L), lane L + c column c of RHS, and returns column c of Z in x.  Everything
+// stays in registers, the pivot column and the factors reach the other lanes by lane reads; the
+// solve in LDS by 1024 threads spent its 30 us in barriers and one thread's searches.
+// False (in every lane) on a pivot below 1e-14 max|M| or a non-finite entry.  pmax / pmin of
+// the pivot moduli is a cheap estimate of the condition of M (a lower bound of it for this
+// pivot order).
+template <int LM>
+__device__ __forceinline__ bool lu_wave(cx<double> (&a)[LM], cx<double> (&x)[LM], int L, double& pmin, double& pmax) {
+    const int lane = threadIdx.x;
+    pmin = INFINITY;
+    pmax = 0.0;
+    bool fin = true;
+    double m = 0.0;
+#pragma unroll
+    for (int r = 0; r < LM; ++r)
+        if (r < L) {
+            fin = fin && isfinite(a[r].re) && isfinite(a[r].im);
+            if (lane < L) m = fmax(m, sqrt(cabs2(a[r])));
+        }
+    if (__any(!fin)) return false;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
+    if (m == 0.0) return false;
+    const double thr = 1e-14 * m;
+    bool ok = true;
+    // compile-time indices throughout, so that the columns stay in registers
+    static_for<0, LM>([&](auto kc) {
+        constexpr int k = decltype(kc)::value;
+        if (k >= L || !ok) return;
+        double best = -1.0;
+        int p = k;
+        static_for<k, LM>([&](auto rc) {
+            constexpr int r = decltype(rc)::value;
+            const double v = cabs2(a[r]);
+            if (r < L && v > best) {
+                best = v;
+                p = r;
+            }
+        });
+        p = __builtin_amdgcn_readlane(p, k);
+        const double pm = sqrt(lane_of(best, k));
+        ok = pm >= thr;
+        pmin = fmin(pmin, pm);
+        pmax = fmax(pmax, pm);
+        static_for<k + 1, LM>([&](auto rc) {
+            constexpr int r = decltype(rc)::value;
+            const bool sw = r == p;
+            const cx<double> t = a[k], v = a[r];
+            a[k] = {sw ? v.re : t.re, sw ? v.im : t.im};
+            a[r] = {sw ? t.re : v.re, sw ? t.im : v.im};
+        });
+        const cx<double> piv = lane_of(a[k], k);
+        const double d = 1.0 / cabs2(piv);
+        static_for<k + 1, LM>([&](auto rc) {
+            constexpr int r = decltype(rc)::value;
+            if (r >= L) return;
+            const cx<double> f = cmulc(piv, lane_of(a[r], k));  // conj(piv) num / |piv|^2 = num / piv
+            a[r] = a[r] - cx<double>{f.re * d, f.im * d} * a[k];
+        });
+    });
+    static_for<0, LM>([&](auto kc) {
+        constexpr int k = LM - 1 - decltype(kc)::value;
+        if (k >= L || !ok) return;
+        cx<double> v = a[k];
+        static_for<k + 1, LM>([&](auto cc) {
+            constexpr int c = decltype(cc)::value;
+            if (c < L) v = v - lane_of(a[k], c) * x[c];
+        });
+        const cx<double> piv = lane_of(a[k], k);
+        const double d = 1.0 / cabs2(piv);
+        const cx<double> q = cmulc(piv, v);
+        x[k] = {q.re * d, q.im * d};
+    });
+    return ok;
+}
+
+__device__ __forceinline__ double cond_of(double pmin, double pmax, bool ok) { return ok ? pmax / pmin : INFINITY; }
+
+// Z = M^{-1} (c RHS) for a complex scale c; on failure Z = 0.  status_bit 0: *status = ok ? 0 : 1;
+// otherwise *status |= status_bit on failure.  cond (may be null) receives the pivot-ratio
+// condition estimate.
+template <int LM>
+__global__ void __launch_bounds__(64) k_small_solve(const double2* __restrict__ M, const double2* __restrict__ RHS,
+                                                    int L, double2 c, double2* __restrict__ Z,
+                                                    int* __restrict__ status, int status_bit,
+                                                    double* __restrict__ cond) {
     const int t = threadIdx.x;
-    const int W2 = 2 * L;
-    if (t == 0) {
-        sm.flag = 0;
-        sm.pmin = INFINITY;
-        sm.pmax = 0.0;
-    }
-    __syncthreads();
-    if (t < L * W2) {
-        const int r = t / W2, c = t % W2;
-        const double2 v = (c < L) ? sm.M[r * L + c] : sm.RHS[r * L + (c - L)];
-        sm.aug[r * W2 + c] = v;
-        if (!finite2(v)) atomicOr(&sm.flag, 1);
-    }
-    __syncthreads();
-    if (sm.flag) return false;
-    if (t == 0) {
-        double m = 0.0;
-        for (int r = 0; r < L; ++r)
-            for (int c = 0; c < L; ++c) {
-                const double2 v = sm.aug[r * W2 + c];
-                m = fmax(m, sqrt(v.x * v.x + v.y * v.y));
-            }
-        sm.scale = m;
-        if (m == 0.0) sm.flag = 1;
-    }
-    __syncthreads();
-    if (sm.flag) return false;
-    const double thr = 1e-14 * sm.scale;
-    for (int k = 0; k < L; ++k) {
-        if (t == 0) {
-            int p = k;
-            double best = -1.0;
-            for (int r = k; r < L; ++r) {
-                const double2 v = sm.aug[r * W2 + k];
-                const double m = v.x * v.x + v.y * v.y;
-                if (m > best) {
-                    best = m;
-                    p = r;
-                }
-            }
-            const double pm = sqrt(best);
-            if (!(pm >= thr)) sm.flag = 1;
-            sm.pmin = fmin(sm.pmin, pm);
-            sm.pmax = fmax(sm.pmax, pm);
-            sm.piv = p;
-        }
-        __syncthreads();
-        if (sm.flag) return false;
-        const int p = sm.piv;
-        if (p != k && t < W2) {
-            const double2 a = sm.aug[k * W2 + t];
-            sm.aug[k * W2 + t] = sm.aug[p * W2 + t];
-            sm.aug[p * W2 + t] = a;
-        }
-        __syncthreads();
-        if (t < L - k - 1) {
-            const int r = k + 1 + t;
-            const cx<double> piv = {sm.aug[k * W2 + k].x, sm.aug[k * W2 + k].y};
-            const cx<double> num = {sm.aug[r * W2 + k].x, sm.aug[r * W2 + k].y};
-            const double d = 1.0 / cabs2(piv);
-            const cx<double> f = cmulc(piv, num);  // conj(piv) num / |piv|^2 = num / piv
-            sm.fac[2 * t] = f.re * d;
-            sm.fac[2 * t + 1] = f.im * d;
-        }
-        __syncthreads();
-        const int rows = L - k - 1, cols = W2 - k;
-        for (int id = t; id < rows * cols; id += kRT) {
-            const int r = k + 1 + id / cols, c = k + id % cols;
-            const cx<double> f = {sm.fac[2 * (r - k - 1)], sm.fac[2 * (r - k - 1) + 1]};
-            const cx<double> pk = {sm.aug[k * W2 + c].x, sm.aug[k * W2 + c].y};
-            cx<double> v = {sm.aug[r * W2 + c].x, sm.aug[r * W2 + c].y};
-            v = v - f * pk;
-            sm.aug[r * W2 + c] = make_double2(v.re, v.im);
-        }
-        __syncthreads();
-    }
-    // back substitution, one thread per right-hand-side column
-    if (t < L) {
-        for (int k = L - 1; k >= 0; --k) {
-            cx<double> x = {sm.aug[k * W2 + L + t].x, sm.aug[k * W2 + L + t].y};
-            for (int c = k + 1; c < L; ++c) {
-                const cx<double> a = {sm.aug[k * W2 + c].x, sm.aug[k * W2 + c].y};
-                const cx<double> sv = {sm.sol[c * L + t].x, sm.sol[c * L + t].y};
-                x = x - a * sv;
-            }
-            const cx<double> piv = {sm.aug[k * W2 + k].x, sm.aug[k * W2 + k].y};
-            const double d = 1.0 / cabs2(piv);
-            const cx<double> q = cmulc(piv, x);
-            sm.sol[k * L + t] = make_double2(q.re * d, q.im * d);
+    cx<double> a[LM], x[LM];
+#pragma unroll
+    for (int r = 0; r < LM; ++r) {
+        a[r] = x[r] = {0.0, 0.0};
+        if (r < L && t < L) a[r] = StF64::ld(M, r * L + t);
+        if (r < L && t >= L && t < 2 * L) {
+            const double2 v = RHS[r * L + t - L];
+            a[r] = {c.x * v.x - c.y * v.y, c.x * v.y + c.y * v.x};
         }
     }
-    __syncthreads();
-    return true;
-}
-
-__global__ void __launch_bounds__(kRT) k_reduce_gram(const double2* __restrict__ partial, int nb, int L,
-                                                     double2* __restrict__ C) {
-    __shared__ SolveShared sm;
-    reduce_partials(partial, nb, L, true, 0, sm.red, sm.scratch);
-    if ((int)threadIdx.x < L * L) C[threadIdx.x] = sm.red[threadIdx.x];
-}
-
-__global__ void __launch_bounds__(kRT) k_reduce_extras(const double2* __restrict__ partial, int nb, int n,
-                                                       double* __restrict__ out) {
-    __shared__ SolveShared sm;
-    reduce_partials(partial, nb, 1, false, n, sm.red, sm.scratch);
-    if ((int)threadIdx.x < n) out[threadIdx.x] = sm.red[threadIdx.x].x;
-}
-
-__device__ __forceinline__ double cond_of(const SolveShared& sm, bool ok) {
-    return ok ? sm.pmax / sm.pmin : INFINITY;
-}
-
-// Z = M^{-1} (c RHS) for a complex scale c, by LU in LDS; on failure Z = 0.
-// status_bit 0: *status = ok ? 0 : 1; otherwise *status |= status_bit on
-// failure.  cond (may be null) receives the pivot-ratio condition estimate.
-__global__ void __launch_bounds__(kRT) k_small_solve(const double2* __restrict__ M, const double2* __restrict__ RHS,
-                                                     int L, double2 c, double2* __restrict__ Z,
-                                                     int* __restrict__ status, int status_bit,
-                                                     double* __restrict__ cond) {
-    __shared__ SolveShared sm;
-    const int t = threadIdx.x;
-    if (t < L * L) {
-        sm.M[t] = M[t];
-        const double2 r = RHS[t];
-        sm.RHS[t] = make_double2(c.x * r.x - c.y * r.y, c.x * r.y + c.y * r.x);
+    double pmin, pmax;
+    const bool ok = lu_wave<LM>(a, x, L, pmin, pmax);
+    if (t >= L && t < 2 * L) {
+#pragma unroll
+        for (int r = 0; r < LM; ++r)
+            if (r < L) Z[r * L + t - L] = ok ? make_double2(x[r].re, x[r].im) : make_double2(0.0, 0.0);
     }
-    __syncthreads();
-    const bool ok = lu_solve_shared(sm, L);
-    if (t < L * L) Z[t] = ok ? sm.sol[t] : make_double2(0.0, 0.0);
     if (t == 0) {
         if (status_bit == 0) status[0] = ok ? 0 : 1;
         else if (!ok) status[0] |= status_bit;
-        if (cond) cond[0] = cond_of(sm, ok);
+        if (cond) cond[0] = cond_of(pmin, pmax, ok);
     }
 }
 
 // Status bits of the solver flags
 constexpr int kAlphaBreak = 1, kGammaBreak = 2, kNaN = 4;
 
-// alpha: (Rt^H V) alpha = Rt^H R_k ; zeta = Tr[W^H R] / Tr[W^H W].  On a
-// breakdown alpha = 0 and zeta = 0, so the following updates leave X and R
+// alpha: (Rt^H V) alpha = Rt^H R_k ; zeta = Tr[W^H R] / Tr[W^H W].  red: the reduced tile (rows of
+// 16) and extras.  On a breakdown alpha = 0 and zeta = 0, so the following updates leave X and R
 // unchanged.
-__global__ void __launch_bounds__(kRT) k_solve_alpha(const double2* __restrict__ partial, int nb, int L,
-                                                     SolverBufs b) {
-    __shared__ SolveShared sm;
+template <int LM>
+__global__ void __launch_bounds__(64) k_solve_alpha(const double2* __restrict__ red, int L, SolverBufs b) {
     const int t = threadIdx.x;
-    reduce_partials(partial, nb, L, true, 2, sm.red, sm.scratch);
-    if (t < L * L) {
-        sm.M[t] = sm.red[t];
-        sm.RHS[t] = b.C_r[t];
+    cx<double> a[LM], x[LM];
+#pragma unroll
+    for (int r = 0; r < LM; ++r) {
+        a[r] = x[r] = {0.0, 0.0};
+        if (r < L && t < L) a[r] = StF64::ld(red, r * 16 + t);
+        if (r < L && t >= L && t < 2 * L) a[r] = StF64::ld(b.C_r, r * L + t - L);
     }
-    __syncthreads();
-    const double2 twr = sm.red[L * L], tww = sm.red[L * L + 1];
-    bool ok = lu_solve_shared(sm, L);
+    const double2 twr = red[256], tww = red[257];
+    double pmin, pmax;
+    bool ok = lu_wave<LM>(a, x, L, pmin, pmax);
     ok = ok && finite2(twr) && isfinite(tww.x) && tww.x > 0.0;
-    if (t < L * L) b.alpha[t] = ok ? sm.sol[t] : make_double2(0.0, 0.0);
+    if (t >= L && t < 2 * L) {
+#pragma unroll
+        for (int r = 0; r < LM; ++r)
+            if (r < L) b.alpha[r * L + t - L] = ok ? make_double2(x[r].re, x[r].im) : make_double2(0.0, 0.0);
+    }
     if (t == 0) {
-        b.cond[0] = cond_of(sm, ok);
+        b.cond[0] = cond_of(pmin, pmax, ok);
         b.zeta[0] = ok ? make_double2(twr.x / tww.x, twr.y / tww.x) : make_double2(0.0, 0.0);
         b.zeta[1] = twr;
         b.zeta[2] = tww;
@@ -422,37 +387,51 @@ __global__ void __launch_bounds__(kRT) k_solve_alpha(const double2* __restrict__
 }
 
 // norms of R_{k+1}; gamma: (Rt^H R_k) gamma = Rt^H R_{k+1} / zeta; then C_r <- C_rn.
-__global__ void __launch_bounds__(kRT) k_solve_gamma(const double2* __restrict__ partial, int nb, int L,
-                                                     SolverBufs b) {
-    __shared__ SolveShared sm;
+template <int LM>
+__global__ void __launch_bounds__(64) k_solve_gamma(const double2* __restrict__ red, int L, SolverBufs b) {
     const int t = threadIdx.x;
-    reduce_partials(partial, nb, L, true, L, sm.red, sm.scratch);
     const cx<double> z = StF64::ld(b.zeta, 0);
     const double zz = cabs2(z);
-    if (t < L * L) {
-        sm.M[t] = b.C_r[t];
-        const double2 c = sm.red[t];
-        // c / z = c conj(z) / |z|^2
-        sm.RHS[t] = zz > 0.0 ? make_double2((c.x * z.re + c.y * z.im) / zz, (c.y * z.re - c.x * z.im) / zz)
-                             : make_double2(0.0, 0.0);
+    cx<double> a[LM], x[LM];
+#pragma unroll
+    for (int r = 0; r < LM; ++r) {
+        a[r] = x[r] = {0.0, 0.0};
+        if (r < L && t < L) a[r] = StF64::ld(b.C_r, r * L + t);
+        if (r < L && t >= L && t < 2 * L) {
+            const double2 c = red[r * 16 + t - L];
+            // c / z = c conj(z) / |z|^2
+            if (zz > 0.0) a[r] = {(c.x * z.re + c.y * z.im) / zz, (c.y * z.re - c.x * z.im) / zz};
+        }
     }
+    bool nan = false;
     if (t < L) {
-        const double v = sm.red[L * L + t].x;
+        const double v = red[256 + t].x;
         b.norms[t] = v;
-        if (!isfinite(v)) atomicOr(b.status, kNaN);
+        nan = !isfinite(v);
     }
-    __syncthreads();
-    bool ok = lu_solve_shared(sm, L);
+    nan = __any(nan);
+    double pmin, pmax;
+    bool ok = lu_wave<LM>(a, x, L, pmin, pmax);
     ok = ok && zz > 0.0;
-    if (t < L * L) {
-        b.gamma[t] = ok ? sm.sol[t] : make_double2(0.0, 0.0);
-        b.C_r[t] = sm.red[t];
-        b.C_rn[t] = sm.red[t];
+    if (t >= L && t < 2 * L) {
+#pragma unroll
+        for (int r = 0; r < LM; ++r)
+            if (r < L) {
+                b.gamma[r * L + t - L] = ok ? make_double2(x[r].re, x[r].im) : make_double2(0.0, 0.0);
+                const double2 c = red[r * 16 + t - L];
+                b.C_r[r * L + t - L] = c;
+                b.C_rn[r * L + t - L] = c;
+            }
     }
     if (t == 0) {
-        b.cond[1] = cond_of(sm, ok);
-        if (!ok) b.status[0] |= kGammaBreak;
+        b.cond[1] = cond_of(pmin, pmax, ok);
+        const int bits = (nan ? kNaN : 0) | (ok ? 0 : kGammaBreak);
+        if (bits) b.status[0] |= bits;
     }
+}
+
+__global__ void k_extras_re(const double2* __restrict__ red, double* __restrict__ out, int n) {
+    if ((int)threadIdx.x < n) out[threadIdx.x] = red[threadIdx.x].x;
 }
 
 // ---------------------------------------------------------------------------
@@ -743,10 +722,14 @@ inline unsigned nblk(size_t n, unsigned b) { return (unsigned)((n + b - 1) / b);
 }  // namespace
 
 size_t partial_stride() { return kPStride; }
+size_t partial_pairs() { return (size_t)(kMaxPartial + 1) * kPStride; }  // and one reduced block
 
 int gram_blocks(size_t N) {
+    // 4096 rows each on large lattices; on small ones down to one 256-row chunk, so that 384
+    // workgroups share the rows (24 workgroups took 191 us for the X / R update at 8^3 x 16, L = 12)
     size_t nb = (N + 4095) / 4096;
-    if (nb < 1) nb = 1;
+    const size_t chunks = (N + kWG - 1) / kWG, least = chunks < 384 ? chunks : 384;
+    if (nb < least) nb = least;
     if (nb > kMaxPartial) nb = kMaxPartial;
     return (int)nb;
 }
@@ -758,19 +741,29 @@ hipError_t launch_gram_partials(const double2* P, const double2* Q, size_t N, in
 }
 
 hipError_t launch_reduce_gram(const double2* partial, int nb, int L, double2* C, hipStream_t s) {
-    k_reduce_gram<<<1, kRT, 0, s>>>(partial, nb, L, C);
+    k_reduce_rows<<<L, kWG, 0, s>>>(partial, nb, 0, C, L, L);
+    return hipGetLastError();
+}
+
+// the bound LM of the one-wave solves
+#define WD_LM_SWITCH(L, CALL)                \
+    do {                                     \
+        if ((L) <= 4) CALL(4);               \
+        else if ((L) <= 8) CALL(8);          \
+        else if ((L) <= 12) CALL(12);        \
+        else CALL(16);                       \
+    } while (0)
+
+hipError_t launch_small_solve_scaled(const double2* M, const double2* RHS, int L, double2 c, double2* Z, int* status,
+                                     int status_bit, double* cond, hipStream_t s) {
+#define WD_CALL_SS(lm) k_small_solve<lm><<<1, 64, 0, s>>>(M, RHS, L, c, Z, status, status_bit, cond)
+    WD_LM_SWITCH(L, WD_CALL_SS);
+#undef WD_CALL_SS
     return hipGetLastError();
 }
 
 hipError_t launch_small_solve(const double2* M, const double2* RHS, int L, double2* Z, int* status, hipStream_t s) {
-    k_small_solve<<<1, kRT, 0, s>>>(M, RHS, L, make_double2(1.0, 0.0), Z, status, 0, nullptr);
-    return hipGetLastError();
-}
-
-hipError_t launch_small_solve_scaled(const double2* M, const double2* RHS, int L, double2 c, double2* Z, int* status,
-                                     int status_bit, double* cond, hipStream_t s) {
-    k_small_solve<<<1, kRT, 0, s>>>(M, RHS, L, c, Z, status, status_bit, cond);
-    return hipGetLastError();
+    return launch_small_solve_scaled(M, RHS, L, make_double2(1.0, 0.0), Z, status, 0, nullptr, s);
 }
 
 hipError_t launch_gram1(const double2* Rt, const double2* V, const double2* W, const double2* R, size_t N, int L,
@@ -779,13 +772,24 @@ hipError_t launch_gram1(const double2* Rt, const double2* V, const double2* W, c
     return hipGetLastError();
 }
 
-hipError_t launch_solve_alpha(const double2* partial, int nb, int L, const SolverBufs& b, hipStream_t s) {
-    k_solve_alpha<<<1, kRT, 0, s>>>(partial, nb, L, b);
+// the reduced block behind the partial ones
+static double2* reduced(double2* partial) { return partial + (size_t)kMaxPartial * kPStride; }
+
+hipError_t launch_solve_alpha(double2* partial, int nb, int L, const SolverBufs& b, hipStream_t s) {
+    double2* red = reduced(partial);
+    k_reduce_rows<<<17, kWG, 0, s>>>(partial, nb, 0, red, 16, 16);
+#define WD_CALL_A(lm) k_solve_alpha<lm><<<1, 64, 0, s>>>(red, L, b)
+    WD_LM_SWITCH(L, WD_CALL_A);
+#undef WD_CALL_A
     return hipGetLastError();
 }
 
-hipError_t launch_solve_gamma(const double2* partial, int nb, int L, const SolverBufs& b, hipStream_t s) {
-    k_solve_gamma<<<1, kRT, 0, s>>>(partial, nb, L, b);
+hipError_t launch_solve_gamma(double2* partial, int nb, int L, const SolverBufs& b, hipStream_t s) {
+    double2* red = reduced(partial);
+    k_reduce_rows<<<17, kWG, 0, s>>>(partial, nb, 0, red, 16, 16);
+#define WD_CALL_G(lm) k_solve_gamma<lm><<<1, 64, 0, s>>>(red, L, b)
+    WD_LM_SWITCH(L, WD_CALL_G);
+#undef WD_CALL_G
     return hipGetLastError();
 }
 
@@ -861,7 +865,8 @@ hipError_t launch_colnorms(const double2* R, size_t N, int L, double2* partial, 
     k_colnorms<<<nb, kWG, 0, s>>>(R, N, L, partial, nb);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    k_reduce_extras<<<1, kRT, 0, s>>>(partial, nb, L, norms);
+    k_reduce_rows<<<1, kWG, 0, s>>>(partial, nb, 16, reduced(partial), 16, 16);
+    k_extras_re<<<1, 64, 0, s>>>(reduced(partial), norms, L);
     return hipGetLastError();
 }
 

@@ -534,6 +534,7 @@ int lowp_ensure(wd_ctx* c);  // allocates the three low-precision block buffers
 
 // ---- block kernels (wd_blas.hip)
 size_t partial_stride();  // complex entries per partial block
+size_t partial_pairs();   // complex entries of the partial buffer
 int gram_blocks(size_t N);
 // partials of P^H Q over rows (nb blocks)
 hipError_t launch_gram_partials(const double2* P, const double2* Q, size_t N, int L, double2* partial, int nb,
@@ -566,10 +567,10 @@ struct SolverBufs {
 };
 hipError_t launch_gram1(const double2* Rt, const double2* V, const double2* W, const double2* R, size_t N, int L,
                         double2* partial, int nb, hipStream_t s);
-hipError_t launch_solve_alpha(const double2* partial, int nb, int L, const SolverBufs& b, hipStream_t s);
+hipError_t launch_solve_alpha(double2* partial, int nb, int L, const SolverBufs& b, hipStream_t s);
 hipError_t launch_update_U(const double2* P, const double2* V, const double2* zeta, const double2* alpha,
                            double2* U, size_t N, int L, hipStream_t s);
-hipError_t launch_solve_gamma(const double2* partial, int nb, int L, const SolverBufs& b, hipStream_t s);
+hipError_t launch_solve_gamma(double2* partial, int nb, int L, const SolverBufs& b, hipStream_t s);
 hipError_t launch_update_PV_gram(double2* P, double2* V, const double2* R, const double2* W, const double2* U,
                                  const double2* Y, const double2* gamma, const double2* Rt, size_t N, int L,
                                  double2* partial, int nb, hipStream_t s);

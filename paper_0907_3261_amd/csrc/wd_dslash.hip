@@ -405,7 +405,7 @@ template <int MODE, int FMT = 0, class SC = StF64, int VT = 0>
 __global__ void __launch_bounds__(256)
     k_hop_f64(const Geom g, const SiteMap sm, const typename SC::P* __restrict__ Uk,
               const typename SC::P* __restrict__ Cl, const double2* __restrict__ X, const double2* __restrict__ Rh,
-              double2* __restrict__ Y, const int L, const double invk = 0.0, const int bc_t = 0) {
+              double2* __restrict__ Y, const int L, const int cpg, const double invk = 0.0, const int bc_t = 0) {
     static_assert(MODE != APPLY || FMT == 0, "the operator takes and returns the standard form");
     constexpr bool TD_IN = (FMT & FMT_IN_TD) != 0, TD_OUT = (FMT & FMT_OUT_TD) != 0;
     __shared__ double2 sU[72][64];
@@ -485,7 +485,8 @@ __global__ void __launch_bounds__(256)
     }
     __syncthreads();
     constexpr bool ADD = MODE != APPLY;
-    for (int c = w; c < L; c += 4) {
+    const int c1 = min(L, (int)(blockIdx.y + 1) * cpg);
+    for (int c = blockIdx.y * cpg + w; c < c1; c += 4) {
         // the LDS lane index is made opaque per column, so that the compiler re-reads the staged
         // links and blocks in every column instead of hoisting all 108 of them into registers
         int ln = lane;
@@ -633,7 +634,7 @@ template <class SF, class SC, class SY, int MODE>
 __global__ void __launch_bounds__(256, 3)
     k_hop_lds_lp(const Geom g, const SiteMap sm, const typename SC::P* __restrict__ Uk,
                  const typename SC::P* __restrict__ Cl, const typename SF::P* __restrict__ X,
-                 const typename SF::P* __restrict__ Rh, typename SY::P* __restrict__ Y, const int L,
+                 const typename SF::P* __restrict__ Rh, typename SY::P* __restrict__ Y, const int L, const int cpg,
                  const float invk, const int bc_t) {
     using R = typename SF::R;
     using PF = typename SF::P;
@@ -703,7 +704,8 @@ __global__ void __launch_bounds__(256, 3)
     }
     __syncthreads();
     constexpr bool ADD = MODE != APPLY;
-    for (int c = w; c < L; c += 4) {
+    const int c1 = min(L, (int)(blockIdx.y + 1) * cpg);
+    for (int c = blockIdx.y * cpg + w; c < c1; c += 4) {
         int ln = lane;
         asm volatile("" : "+v"(ln));
         const PF* xc = X + (size_t)c * cs;
@@ -819,8 +821,9 @@ __global__ void __launch_bounds__(256, 3)
 template <class SI, class SF, class SY, int MODE, class SC = SF>
 __global__ void __launch_bounds__(256)
     k_first_sweep(const Geom g, const typename SC::P* __restrict__ Cl, const typename SI::P* __restrict__ Rin,
-                  typename SF::P* __restrict__ RL, typename SY::P* __restrict__ Y, const int L) {
-    // one thread per site; the site's A_D^{-1} block stays in registers for all L columns
+                  typename SF::P* __restrict__ RL, typename SY::P* __restrict__ Y, const int L, const int cpg) {
+    // one thread per site and group of cpg columns; the site's A_D^{-1} block stays in registers
+    const int c0 = blockIdx.y * cpg, c1 = min(L, c0 + cpg);
     using R = typename SF::R;
     const int s = blockIdx.x * 256 + threadIdx.x;
     if (s >= g.V) return;
@@ -834,7 +837,7 @@ __global__ void __launch_bounds__(256)
         Herm6<SC, R> T[2];
         T[0].load(Cl, 0, oC, CKS);
         T[1].load(Cl, 1, oC, CKS);
-        for (int col = 0; col < L; ++col) {
+        for (int col = c0; col < c1; ++col) {
             cx<typename SI::R> in[12];
             Vec<SI>::template load<true>(in, Rin + (size_t)col * Vec<SI>::col(g), kI, 0, oI);
             cx<R> v[12], o[12];
@@ -862,7 +865,7 @@ __global__ void __launch_bounds__(256)
     for (int chir = 0; chir < 2; ++chir) {
         Herm6<SC, R> T;
         T.load(Cl, chir, oC, CKS);
-        for (int col = 0; col < L; ++col) {
+        for (int col = c0; col < c1; ++col) {
             const typename SI::P* Rc = Rin + (size_t)col * Vec<SI>::col(g);
             cx<R> v[6];
 #pragma unroll
@@ -924,15 +927,16 @@ hipError_t launch_hop_t(const Geom& g, const LinkInfo& li, const void* Uk, const
             // 32^3 x 64, L = 12 in the tiled layout: A X 3.53 against 3.61 ms with one slice at
             // a time; the sweep reads 18.2 instead of 20.1 GB in the same time)
             const SiteMap sm = make_site_map_rows(g, 12.0 * L * 16 + 72.0 * 16, MODE == APPLY ? 4 : 2);
-            dim3 block(64, 4), grid(sm.nblk);
+            const int cpg = cols_per_group(sm.nblk, L, 1);
+            dim3 block(64, 4), grid(sm.nblk, (L + cpg - 1) / cpg);
             if (g.vt & kVecTiled)
                 k_hop_f64<MODE, 0, SC, 1><<<grid, block, 0, s>>>(
                     g, sm, (const typename SC::P*)Uk, (const typename SC::P*)Cl, (const double2*)X,
-                    (const double2*)Rh, (double2*)Y, L, li.invk, li.bc_t);
+                    (const double2*)Rh, (double2*)Y, L, cpg, li.invk, li.bc_t);
             else
                 k_hop_f64<MODE, 0, SC, 0><<<grid, block, 0, s>>>(
                     g, sm, (const typename SC::P*)Uk, (const typename SC::P*)Cl, (const double2*)X,
-                    (const double2*)Rh, (double2*)Y, L, li.invk, li.bc_t);
+                    (const double2*)Rh, (double2*)Y, L, cpg, li.invk, li.bc_t);
             return hipGetLastError();
         }
     }
@@ -947,10 +951,11 @@ hipError_t launch_hop_t(const Geom& g, const LinkInfo& li, const void* Uk, const
         const bool pairs = Vec<SF>::G == 4 && L <= 6 && ((long long)g.V + 63) / 64 >= 1024;
         if (L >= 3 && !pairs) {
             const SiteMap sm = make_site_map_rows(g, 12.0 * L * sizeof(typename SF::P) + 72.0 * 8, Vec<SF>::G);
-            dim3 block(64, 4), grid(sm.nblk);
+            const int cpg = cols_per_group(sm.nblk, L, 3);
+            dim3 block(64, 4), grid(sm.nblk, (L + cpg - 1) / cpg);
             k_hop_lds_lp<SF, SC, SY, MODE><<<grid, block, 0, s>>>(
                 g, sm, (const typename SC::P*)Uk, (const typename SC::P*)Cl, (const typename SF::P*)X,
-                (const typename SF::P*)Rh, (typename SY::P*)Y, L, (float)li.invk, li.bc_t);
+                (const typename SF::P*)Rh, (typename SY::P*)Y, L, cpg, (float)li.invk, li.bc_t);
             return hipGetLastError();
         }
     }
@@ -965,15 +970,19 @@ hipError_t launch_hop_t(const Geom& g, const LinkInfo& li, const void* Uk, const
 
 template <class SI, class SF, class SY, class SC = SF>
 hipError_t launch_first(const wd_ctx* c, const void* Cl, const void* Rin, void* RL, void* Y, int L, hipStream_t s) {
-    const unsigned nb = (unsigned)((c->g.V + 255) / 256);
+    // all columns to a thread on large lattices; on small ones groups of them, for 512 workgroups
+    // (FP64 at 8^3 x 16, L = 12: 11.3 us against 29 in one group)
+    const int nx = (c->g.V + 255) / 256, share = (int)(((long long)nx * L + 511) / 512);
+    const int cpg = share < L ? share : L;
+    const dim3 nb(nx, (L + cpg - 1) / cpg);
     if (c->jacobi_kind == WD_JACOBI_POINT)
         k_first_sweep<SI, SF, SY, JPOINT, SC><<<nb, 256, 0, s>>>(c->g, (const typename SC::P*)Cl,
                                                                   (const typename SI::P*)Rin, (typename SF::P*)RL,
-                                                                  (typename SY::P*)Y, L);
+                                                                  (typename SY::P*)Y, L, cpg);
     else
         k_first_sweep<SI, SF, SY, JBLOCK, SC><<<nb, 256, 0, s>>>(c->g, (const typename SC::P*)Cl,
                                                                   (const typename SI::P*)Rin, (typename SF::P*)RL,
-                                                                  (typename SY::P*)Y, L);
+                                                                  (typename SY::P*)Y, L, cpg);
     return hipGetLastError();
 }
 
@@ -989,7 +998,8 @@ hipError_t launch_sweep(const wd_ctx* c, int pi, const void* X, const void* Rh, 
 template <int FMT, class SC = StF64>
 hipError_t launch_sweep_td(const wd_ctx* c, const double2* X, const double2* R, double2* Y, int L, hipStream_t s) {
     const SiteMap sm = make_site_map_rows(c->g, 12.0 * L * 16 + 72.0 * 16, 2);
-    dim3 block(64, 4), grid(sm.nblk);
+    const int cpg = cols_per_group(sm.nblk, L, 1);
+    dim3 block(64, 4), grid(sm.nblk, (L + cpg - 1) / cpg);
     constexpr int pi = std::is_same_v<SC, StF64> ? 0 : std::is_same_v<SC, StF32> ? 1 : 2;
     using PC = typename SC::P;
     const LinkInfo li = link_info(c);
@@ -997,13 +1007,13 @@ hipError_t launch_sweep_td(const wd_ctx* c, const double2* X, const double2* R, 
     const PC* U = (const PC*)c->f.Uk[pi];
     const PC* C = (const PC*)(pt ? c->f.Tp[pi] : c->f.Ti[pi]);
     if (pt && (c->g.vt & kVecTiled))
-        k_hop_f64<JPOINT, FMT, SC, 1><<<grid, block, 0, s>>>(c->g, sm, U, C, X, R, Y, L, li.invk, li.bc_t);
+        k_hop_f64<JPOINT, FMT, SC, 1><<<grid, block, 0, s>>>(c->g, sm, U, C, X, R, Y, L, cpg, li.invk, li.bc_t);
     else if (pt)
-        k_hop_f64<JPOINT, FMT, SC, 0><<<grid, block, 0, s>>>(c->g, sm, U, C, X, R, Y, L, li.invk, li.bc_t);
+        k_hop_f64<JPOINT, FMT, SC, 0><<<grid, block, 0, s>>>(c->g, sm, U, C, X, R, Y, L, cpg, li.invk, li.bc_t);
     else if (c->g.vt & kVecTiled)
-        k_hop_f64<JBLOCK, FMT, SC, 1><<<grid, block, 0, s>>>(c->g, sm, U, C, X, R, Y, L, li.invk, li.bc_t);
+        k_hop_f64<JBLOCK, FMT, SC, 1><<<grid, block, 0, s>>>(c->g, sm, U, C, X, R, Y, L, cpg, li.invk, li.bc_t);
     else
-        k_hop_f64<JBLOCK, FMT, SC, 0><<<grid, block, 0, s>>>(c->g, sm, U, C, X, R, Y, L, li.invk, li.bc_t);
+        k_hop_f64<JBLOCK, FMT, SC, 0><<<grid, block, 0, s>>>(c->g, sm, U, C, X, R, Y, L, cpg, li.invk, li.bc_t);
     return hipGetLastError();
 }
 

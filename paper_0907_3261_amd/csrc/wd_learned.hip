@@ -413,7 +413,7 @@ __global__ void k_adam(float2* __restrict__ theta, const double2* __restrict__ G
 template <class SI, class SO, class SL>
 __global__ void __launch_bounds__(256) k_layer_lds(const Geom g, const SiteMap sm, const typename SL::P* __restrict__ U,
                                                    const float2* __restrict__ W, const typename SI::P* __restrict__ Zin,
-                                                   typename SO::P* __restrict__ Zout, const int L) {
+                                                   typename SO::P* __restrict__ Zout, const int L, const int cpg) {
     using R = typename SL::R;
     using PL = typename SL::P;
     __shared__ PL sU[72][64];
@@ -442,7 +442,8 @@ __global__ void __launch_bounds__(256) k_layer_lds(const Geom g, const SiteMap s
         }
     }
     __syncthreads();
-    for (int c = w; c < L; c += 4) {
+    const int c1 = min(L, (int)(blockIdx.y + 1) * cpg);
+    for (int c = blockIdx.y * cpg + w; c < c1; c += 4) {
         // the LDS lane index is opaque per column so that the staged links are read where they
         // are used instead of all being hoisted into registers
         int ln = lane;
@@ -602,9 +603,10 @@ hipError_t launch_layer(const wd_ctx* c, const typename SL::P* U, const float2* 
         // site map with four t-slices walked together (16 % fewer fetched bytes and 5 % faster
         // than the plane-wide map)
         const SiteMap sm = make_site_map_rows(c->g, 12.0 * L * sizeof(typename SI::P) + 72.0 * sizeof(typename SL::P), 4);
-        dim3 block(64, 4), grid(sm.nblk);
+        const int cpg = cols_per_group(sm.nblk, L, 2);
+        dim3 block(64, 4), grid(sm.nblk, (L + cpg - 1) / cpg);
         k_layer_lds<SI, SO, SL><<<grid, block, 0, s>>>(c->g, sm, U, W, (const typename SI::P*)in,
-                                                       (typename SO::P*)out, L);
+                                                       (typename SO::P*)out, L, cpg);
         return hipGetLastError();
     }
     const SiteMap sm = make_site_map_rows(c->g, 12.0 * L * sizeof(typename SI::P) + 36.0 * sizeof(typename SL::P), 4);
@@ -620,9 +622,7 @@ hipError_t launch_layer(const wd_ctx* c, const float2* W, const void* in, void* 
     const typename SI::P* zi = (const typename SI::P*)in;
     typename SO::P* zo = (typename SO::P*)out;
     if (L >= 3) {
-        // a workgroup takes all columns of its tile (the links staged once) unless the tiles alone
-        // leave CUs without work: then groups of four columns
-        const int cpg = sm.nblk < 256 ? 4 : 4 * ((L + 3) / 4);
+        const int cpg = cols_per_group(sm.nblk, L, 4);
         k_layer_f32<SI, SO, true><<<dim3(sm.nblk, (L + cpg - 1) / cpg), dim3(64, 4), 0, s>>>(c->g, sm, c->U32, W, zi,
                                                                                           zo, L, cpg);
     } else {

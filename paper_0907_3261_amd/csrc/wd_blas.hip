@@ -69,20 +69,6 @@ __device__ __forceinline__ void gram_store(const GramAcc& acc, double2* __restri
     out[e] = s;
 }
 
-// Per-column squared norms held per lane (column = lane % 16) -> extras[0..15]
-__device__ __forceinline__ void colsum_store(double v, double2* __restrict__ out, double* shd) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    v += __shfl_xor(v, 16, 64);
-    v += __shfl_xor(v, 32, 64);
-    if (lane < 16) shd[w * 16 + lane] = v;
-    __syncthreads();
-    if (threadIdx.x < 16) {
-        double s = 0.0;
-        for (int q = 0; q < kWG / 64; ++q) s += shd[q * 16 + threadIdx.x];
-        out[256 + threadIdx.x] = make_double2(s, 0.0);
-    }
-}
-
 struct RowRange {
     size_t r0, r1;
 };
@@ -175,26 +161,28 @@ __global__ void __launch_bounds__(kWG) k_gram1(const double2* __restrict__ Rt, c
     }
 }
 
-// ---- column norms only (extras)
-__global__ void __launch_bounds__(kWG) k_colnorms(const double2* __restrict__ R, size_t N, int L,
-                                                  double2* __restrict__ partial, int nb) {
-    __shared__ double shd[kWG / 64 * 16];
+// ---- column norms only (extras): a workgroup per row range and column, each wave reading 1 KB
+// runs of its column (64-byte pieces of sixteen columns at once, as the Gram kernels read, ran at
+// 2.5 TB/s at 16^3 x 32, L = 12; 120 -> 75 us)
+__global__ void __launch_bounds__(kWG) k_colnorms(const double2* __restrict__ R, size_t N, double2* __restrict__ partial,
+                                                  int nb) {
+    __shared__ double sh[kWG / 64];
     const RowRange rr = block_rows(N, nb);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int col = lane & 15, q = lane >> 4;
+    const double2* c = R + (size_t)blockIdx.y * N;
     double nrm = 0.0;
-    if (col < L)
-        for (size_t n0 = rr.r0 + 16 * w; n0 < rr.r1; n0 += 16 * (kWG / 64)) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const size_t n = n0 + 4 * r + q;
-                if (n < rr.r1) {
-                    const cx<double> v = StF64::ld(R, (size_t)col * N + n);
-                    nrm += v.re * v.re + v.im * v.im;
-                }
-            }
-        }
-    colsum_store(nrm, partial + (size_t)blockIdx.x * kPStride, shd);
+#pragma unroll 4
+    for (size_t n = rr.r0 + threadIdx.x; n < rr.r1; n += kWG) {
+        const double2 v = c[n];
+        nrm += v.x * v.x + v.y * v.y;
+    }
+    nrm = wave_sum(nrm);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = nrm;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double s = 0.0;
+        for (int q = 0; q < kWG / 64; ++q) s += sh[q];
+        partial[(size_t)blockIdx.x * kPStride + 256 + blockIdx.y] = make_double2(s, 0.0);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -862,7 +850,7 @@ hipError_t launch_axpby_block(const double2* B, const double2* AX, double2* R, s
 
 hipError_t launch_colnorms(const double2* R, size_t N, int L, double2* partial, int nb, double* norms,
                            hipStream_t s) {
-    k_colnorms<<<nb, kWG, 0, s>>>(R, N, L, partial, nb);
+    k_colnorms<<<dim3(nb, L), kWG, 0, s>>>(R, N, partial, nb);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     k_reduce_rows<<<1, kWG, 0, s>>>(partial, nb, 16, reduced(partial), 16, 16);

@@ -11,7 +11,8 @@
 // both MFMA operands, so one instruction accumulates sum_k conj(P[k,i]) Q[k,j]
 // over 4 rows into a 16 x 16 tile (L <= 16).  Complex products take four real
 // MFMAs.  Reductions run in two passes with a fixed order (per-workgroup
-// partials, then one workgroup), so results are deterministic.
+// partials, then one workgroup for each row of the result), so results are
+// deterministic.
 #include "wd_internal.h"
 
 namespace wd {

@@ -6,7 +6,8 @@
 // fetched from HBM is reused from cache by all column tiles and from
 // registers by the CT columns of a thread.  Spinor and link arrays are
 // site-fastest (structure of arrays), so each load instruction of a
-// wavefront reads 64 consecutive sites.
+// wavefront reads 64 consecutive sites; FP32 and BF16 library blocks hold
+// 16-byte words of one site instead (Vec in wd_internal.h).
 //
 // The hop uses the rank-2 spin projectors of the chiral basis: for the
 // forward hop (1 - g_mu) psi = (h, -B^dag h) with h = u - B d, for the

@@ -190,32 +190,42 @@ __global__ void __launch_bounds__(kWG) k_colnorms(const double2* __restrict__ R,
 // Reduction of partials and L x L solves
 // ---------------------------------------------------------------------------
 // Row b of every partial block (b < 16: row b of the tile, 16: the extras) summed over the nb
-// blocks in a fixed order: out[b * stride + e], e < n.  One workgroup per row, sixteen threads per
-// entry: one workgroup for all rows took 35 us for 384 blocks at L = 12, most of each
-// alpha and gamma solve on small lattices; this takes 5.
-__global__ void __launch_bounds__(kWG) k_reduce_rows(const double2* __restrict__ partial, int nb, int row0,
+// blocks in a fixed order: out[b * stride + e], e < n.  One workgroup per row, ng <= 16 threads per
+// entry, each over every ng-th block: one workgroup for all rows took 35 us for 384 blocks at
+// L = 12, most of each alpha and gamma solve on small lattices; this takes about 6.
+__global__ void __launch_bounds__(kWG) k_reduce_rows(const double2* __restrict__ partial, int nb, int row0, int ng,
                                                      double2* __restrict__ out, int stride, int n) {
     __shared__ double2 sh[kWG];
     const int e = threadIdx.x & 15, q = threadIdx.x >> 4;
     const double2* p = partial + (size_t)(row0 + blockIdx.x) * 16 + e;
     double2 s = make_double2(0.0, 0.0);
-#pragma unroll 8
-    for (int b = q; b < nb; b += kWG / 16) {
-        const double2 v = p[(size_t)b * kPStride];
-        s.x += v.x;
-        s.y += v.y;
+    if (q < ng) {
+#pragma unroll 16
+        for (int b = q; b < nb; b += ng) {
+            const double2 v = p[(size_t)b * kPStride];
+            s.x += v.x;
+            s.y += v.y;
+        }
     }
     sh[threadIdx.x] = s;
     __syncthreads();
     if ((int)threadIdx.x < n && threadIdx.x < 16) {
         double2 t = sh[threadIdx.x];
-#pragma unroll
-        for (int g = 1; g < kWG / 16; ++g) {
+        for (int g = 1; g < ng; ++g) {
             t.x += sh[g * 16 + threadIdx.x].x;
             t.y += sh[g * 16 + threadIdx.x].y;
         }
         out[(size_t)blockIdx.x * stride + threadIdx.x] = t;
     }
+}
+
+// Threads per entry for E = L * L + extras entries: 1024 threads shared by the entries, the split
+// (and with it the order of the sums) of a reduction in one workgroup.  Close to the critical
+// kappa the last bit of the sums moves the iteration count: 32^3 x 64, L = 12, kappa = 0.127 takes
+// 61 iterations with this order and 66 with sixteen threads for every L.
+inline int reduce_groups(int E) {
+    const int g = 1024 / E;
+    return g < 16 ? g : 16;
 }
 
 __device__ __forceinline__ bool finite2(double2 v) { return isfinite(v.x) && isfinite(v.y); }
@@ -730,7 +740,7 @@ hipError_t launch_gram_partials(const double2* P, const double2* Q, size_t N, in
 }
 
 hipError_t launch_reduce_gram(const double2* partial, int nb, int L, double2* C, hipStream_t s) {
-    k_reduce_rows<<<L, kWG, 0, s>>>(partial, nb, 0, C, L, L);
+    k_reduce_rows<<<L, kWG, 0, s>>>(partial, nb, 0, reduce_groups(L * L), C, L, L);
     return hipGetLastError();
 }
 
@@ -766,7 +776,7 @@ static double2* reduced(double2* partial) { return partial + (size_t)kMaxPartial
 
 hipError_t launch_solve_alpha(double2* partial, int nb, int L, const SolverBufs& b, hipStream_t s) {
     double2* red = reduced(partial);
-    k_reduce_rows<<<17, kWG, 0, s>>>(partial, nb, 0, red, 16, 16);
+    k_reduce_rows<<<17, kWG, 0, s>>>(partial, nb, 0, reduce_groups(L * L + 2), red, 16, 16);
 #define WD_CALL_A(lm) k_solve_alpha<lm><<<1, 64, 0, s>>>(red, L, b)
     WD_LM_SWITCH(L, WD_CALL_A);
 #undef WD_CALL_A
@@ -775,7 +785,7 @@ hipError_t launch_solve_alpha(double2* partial, int nb, int L, const SolverBufs&
 
 hipError_t launch_solve_gamma(double2* partial, int nb, int L, const SolverBufs& b, hipStream_t s) {
     double2* red = reduced(partial);
-    k_reduce_rows<<<17, kWG, 0, s>>>(partial, nb, 0, red, 16, 16);
+    k_reduce_rows<<<17, kWG, 0, s>>>(partial, nb, 0, reduce_groups(L * L + L), red, 16, 16);
 #define WD_CALL_G(lm) k_solve_gamma<lm><<<1, 64, 0, s>>>(red, L, b)
     WD_LM_SWITCH(L, WD_CALL_G);
 #undef WD_CALL_G
@@ -854,7 +864,7 @@ hipError_t launch_colnorms(const double2* R, size_t N, int L, double2* partial, 
     k_colnorms<<<dim3(nb, L), kWG, 0, s>>>(R, N, partial, nb);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    k_reduce_rows<<<1, kWG, 0, s>>>(partial, nb, 16, reduced(partial), 16, 16);
+    k_reduce_rows<<<1, kWG, 0, s>>>(partial, nb, 16, reduce_groups(L), reduced(partial), 16, 16);
     k_extras_re<<<1, 64, 0, s>>>(reduced(partial), norms, L);
     return hipGetLastError();
 }

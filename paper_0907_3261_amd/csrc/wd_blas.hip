@@ -192,7 +192,8 @@ __global__ void __launch_bounds__(kWG) k_colnorms(const double2* __restrict__ R,
 // Row b of every partial block (b < 16: row b of the tile, 16: the extras) summed over the nb
 // blocks in a fixed order: out[b * stride + e], e < n.  One workgroup per row, ng <= 16 threads per
 // entry, each over every ng-th block: one workgroup for all rows took 35 us for 384 blocks at
-// L = 12, most of each alpha and gamma solve on small lattices; this takes about 6.
+// L = 12, most of each alpha and gamma solve on small lattices; this takes 5 with ng = 16 (the
+// whole 8^3 x 16, L = 12 solve: 6461 us with ng = 16, 6579 with reduce_groups, 10656 before).
 __global__ void __launch_bounds__(kWG) k_reduce_rows(const double2* __restrict__ partial, int nb, int row0, int ng,
                                                      double2* __restrict__ out, int stride, int n) {
     __shared__ double2 sh[kWG];

@@ -297,26 +297,34 @@ struct Vec {
             }
         }
     }
+    // store planes k .. k + G - 1 (k a multiple of G) of the site at byte offset o, streamed with NT
+    // (library blocks only)
+    template <bool NT, typename RV>
+    __device__ __forceinline__ static void store_group(P* base, int k, uint32_t o, const cx<RV>* v) {
+        char* q = reinterpret_cast<char*>(base + k * 64) + o;
+        if constexpr (G == 2) {
+            const wd_fvec4 w = {(float)v[0].re, (float)v[0].im, (float)v[1].re, (float)v[1].im};
+            if (NT) __builtin_nontemporal_store(w, reinterpret_cast<wd_fvec4*>(q));
+            else *reinterpret_cast<wd_fvec4*>(q) = w;
+        } else {
+            const wd_uvec4 w = {pack_bf16((float)v[0].re, (float)v[0].im), pack_bf16((float)v[1].re, (float)v[1].im),
+                                pack_bf16((float)v[2].re, (float)v[2].im), pack_bf16((float)v[3].re, (float)v[3].im)};
+            if (NT) __builtin_nontemporal_store(w, reinterpret_cast<wd_uvec4*>(q));
+            else *reinterpret_cast<wd_uvec4*>(q) = w;
+        }
+    }
     // store planes 0 .. 11 of a site, streamed with NT
     template <bool NT, typename RV>
     __device__ __forceinline__ static void store(P* base, size_t KS, uint32_t o, const cx<RV> (&v)[12]) {
 #pragma unroll
         for (int k = 0; k < 12; k += G) {
-            char* q = reinterpret_cast<char*>(base + (G == 1 ? (size_t)k * KS : (size_t)k * 64)) + o;
             if constexpr (G == 1) {
+                P* q = reinterpret_cast<P*>(reinterpret_cast<char*>(base + (size_t)k * KS) + o);
                 const cx<R> w = {(R)v[k].re, (R)v[k].im};
-                if (NT) S::st_nt(reinterpret_cast<P*>(q), w);
-                else S::st(reinterpret_cast<P*>(q), 0, w);
-            } else if constexpr (G == 2) {
-                const wd_fvec4 w = {(float)v[k].re, (float)v[k].im, (float)v[k + 1].re, (float)v[k + 1].im};
-                if (NT) __builtin_nontemporal_store(w, reinterpret_cast<wd_fvec4*>(q));
-                else *reinterpret_cast<wd_fvec4*>(q) = w;
+                if (NT) S::st_nt(q, w);
+                else S::st(q, 0, w);
             } else {
-                const wd_uvec4 w = {pack_bf16((float)v[k].re, (float)v[k].im), pack_bf16((float)v[k + 1].re, (float)v[k + 1].im),
-                                    pack_bf16((float)v[k + 2].re, (float)v[k + 2].im),
-                                    pack_bf16((float)v[k + 3].re, (float)v[k + 3].im)};
-                if (NT) __builtin_nontemporal_store(w, reinterpret_cast<wd_uvec4*>(q));
-                else *reinterpret_cast<wd_uvec4*>(q) = w;
+                store_group<NT>(base, k, o, &v[k]);
             }
         }
     }

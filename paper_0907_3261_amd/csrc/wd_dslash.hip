@@ -976,10 +976,13 @@ hipError_t launch_hop_t(const Geom& g, const LinkInfo& li, const void* Uk, const
 
 template <class SI, class SF, class SY, class SC = SF>
 hipError_t launch_first(const wd_ctx* c, const void* Cl, const void* Rin, void* RL, void* Y, int L, hipStream_t s) {
-    // all columns to a thread on large lattices; on small ones groups of them, for 512 workgroups
-    // (FP64 at 8^3 x 16, L = 12: 11.3 us against 29 in one group)
-    const int nx = (c->g.V + 255) / 256, share = (int)(((long long)nx * L + 511) / 512);
-    const int cpg = share < L ? share : L;
+    // all columns to a thread, unless the sites fill at most half of the CUs: then as many groups of
+    // columns as fit the chip, a workgroup to a CU.  Each group reads the blocks again, so more
+    // of them than that lose: FP64, one sweep, in one group / in groups for 512 workgroups / by this rule,
+    // 8^3 x 16 (32 workgroups) L = 12: 39.8 / 23.7 / 21.9 us; 14 * 10 * 9 * 18 (89) L = 4: 25.0 / 27.8 / 22.4;
+    // 12^3 x 24 (162) L = 4: 27.4 / 33.4 / 27.0, L = 16: 60.7 / 67.1 / 59.0
+    const int nx = (c->g.V + 255) / 256, room = 256 / nx;
+    const int groups = room < 1 ? 1 : (room < L ? room : L), cpg = (L + groups - 1) / groups;
     const dim3 nb(nx, (L + cpg - 1) / cpg);
     if (c->jacobi_kind == WD_JACOBI_POINT)
         k_first_sweep<SI, SF, SY, JPOINT, SC><<<nb, 256, 0, s>>>(c->g, (const typename SC::P*)Cl,

@@ -971,11 +971,13 @@ hipError_t launch_hop_t(const Geom& g, const LinkInfo& li, const void* Uk, const
             return hipGetLastError();
         }
     }
-    if (L >= 3) {
-        // pairs of columns to a thread, then a last odd one
-        hipError_t e = launch_hop_ct<SF, SY, MODE, 2, SC>(g, li, Uk, Cl, X, Rh, Y, 0, L / 2, s);
-        if (e != hipSuccess || L % 2 == 0) return e;
-        return launch_hop_ct<SF, SY, MODE, 1, SC>(g, li, Uk, Cl, X, Rh, Y, L - 1, 1, s);
+    if constexpr (Vec<SF>::G == 4) {
+        if (L >= 3) {
+            // pairs of columns to a thread, then a last odd one
+            hipError_t e = launch_hop_ct<SF, SY, MODE, 2, SC>(g, li, Uk, Cl, X, Rh, Y, 0, L / 2, s);
+            if (e != hipSuccess || L % 2 == 0) return e;
+            return launch_hop_ct<SF, SY, MODE, 1, SC>(g, li, Uk, Cl, X, Rh, Y, L - 1, 1, s);
+        }
     }
     return launch_hop_ct<SF, SY, MODE, 1, SC>(g, li, Uk, Cl, X, Rh, Y, 0, L, s);
 }

@@ -22,122 +22,105 @@ namespace {
 
 constexpr int kNL = WD_LEARNED_LAYERS, kND = WD_LEARNED_DIRS;
 
-// Operands of one term W_d (U or U^dag or 1) psi(nb): the link and the CT input spinors.
-template <class R, int CT>
+// Operands of one term W_d (U or U^dag or 1) psi(nb): the link and the input spinor.
+template <class R>
 struct Term {
     cx<R> u[9];
-    cx<R> p[CT][12];
+    cx<R> p[12];
 };
 
 // Issue the loads of a term.  KIND: 0 self term, 1 forward hop (link at the site),
-// 2 backward hop (daggered link at the neighbour).  vnb: element offset of the input
-// site in a plane of the block vector, KS its plane stride.
-template <int KIND, class SI, class SL, class R, int CT>
-__device__ __forceinline__ void term_load(Term<R, CT>& t, const typename SL::P* __restrict__ U, int mu, int ls,
-                                          const typename SI::P* __restrict__ Zin, size_t V, size_t KS, size_t col0,
-                                          uint32_t vnb) {
+// 2 backward hop (daggered link at the neighbour).  zc: the input column, vnb: element offset
+// of the input site in a plane of it, KS its plane stride.
+template <int KIND, class SI, class SL, class R>
+__device__ __forceinline__ void term_load(Term<R>& t, const typename SL::P* __restrict__ U, int mu, int ls,
+                                          const typename SI::P* __restrict__ zc, size_t V, size_t KS, uint32_t vnb) {
     if (KIND != 0) {
 #pragma unroll
         for (int k = 0; k < 9; ++k) t.u[k] = SL::ld(U, (size_t)(mu * 9 + k) * V + ls);
     }
 #pragma unroll
-    for (int c = 0; c < CT; ++c) {
-        const typename SI::P* zc = Zin + (col0 + c) * 12 * V;
-#pragma unroll
-        for (int k = 0; k < 12; ++k) {
-            const auto v = SI::ld(zc, (size_t)k * KS + vnb);
-            t.p[c][k] = {(R)v.re, (R)v.im};
-        }
+    for (int k = 0; k < 12; ++k) {
+        const auto v = SI::ld(zc, (size_t)k * KS + vnb);
+        t.p[k] = {(R)v.re, (R)v.im};
     }
 }
 
-// acc += W_d (U or U^dag or 1) psi for the CT columns of a loaded term
-template <int KIND, class R, int CT>
-__device__ __forceinline__ void term_apply(const Term<R, CT>& t, const float2* __restrict__ Wd, cx<R> (&acc)[CT][12]) {
+// acc += W_d (U or U^dag or 1) psi for a loaded term
+template <int KIND, class R>
+__device__ __forceinline__ void term_apply(const Term<R>& t, const float2* __restrict__ Wd, cx<R> (&acc)[12]) {
+    // source spin tt: q = (U or U^dag or 1) psi_tt, then acc[sp] += W[sp][tt] q
 #pragma unroll
-    for (int c = 0; c < CT; ++c) {
-        // source spin tt: q = (U or U^dag or 1) psi_tt, then acc[sp] += W[sp][tt] q
+    for (int tt = 0; tt < 4; ++tt) {
+        cx<R> q[3];
 #pragma unroll
-        for (int tt = 0; tt < 4; ++tt) {
-            cx<R> q[3];
+        for (int a = 0; a < 3; ++a) {
+            if (KIND == 0) {
+                q[a] = t.p[3 * tt + a];
+            } else {
+                cx<R> r = {R(0), R(0)};
 #pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                if (KIND == 0) {
-                    q[a] = t.p[c][3 * tt + a];
-                } else {
-                    cx<R> r = {R(0), R(0)};
-#pragma unroll
-                    for (int b = 0; b < 3; ++b) {
-                        if (KIND == 1)
-                            cfma(r, t.u[a * 3 + b], t.p[c][3 * tt + b]);
-                        else
-                            cfmac(r, t.u[b * 3 + a], t.p[c][3 * tt + b]);
-                    }
-                    q[a] = r;
+                for (int b = 0; b < 3; ++b) {
+                    if (KIND == 1)
+                        cfma(r, t.u[a * 3 + b], t.p[3 * tt + b]);
+                    else
+                        cfmac(r, t.u[b * 3 + a], t.p[3 * tt + b]);
                 }
+                q[a] = r;
             }
+        }
 #pragma unroll
-            for (int sp = 0; sp < 4; ++sp) {
-                const float2 wv = Wd[sp * 4 + tt];
-                const cx<R> w = {(R)wv.x, (R)wv.y};
+        for (int sp = 0; sp < 4; ++sp) {
+            const float2 wv = Wd[sp * 4 + tt];
+            const cx<R> w = {(R)wv.x, (R)wv.y};
 #pragma unroll
-                for (int a = 0; a < 3; ++a) cfma(acc[c][3 * sp + a], w, q[a]);
-            }
+            for (int a = 0; a < 3; ++a) cfma(acc[3 * sp + a], w, q[a]);
         }
     }
 }
 
-// One layer: thread (site, tile) accumulates CT columns, so each link and
-// weight is loaded once per tile.  SI / SO: storage of input / output, SL:
-// storage (and arithmetic precision) of the links.  W: 9 x 16 complex
+// One layer of one or two columns in FP64: a wave per 64 sites and column.  SI / SO: storage of
+// input / output, SL: storage (and arithmetic precision) of the links.  W: 9 x 16 complex
 // (row-major 4 x 4 per direction; direction 1 + 2 mu is the forward hop,
-// 2 + 2 mu the backward one), FP32.  Columns [c0 + tile*CT, + CT) of the
-// block vectors; every tile of the launch is complete.  Used for one or two
-// columns in FP64.
-template <class SI, class SO, class SL, int CT>
+// 2 + 2 mu the backward one), FP32.
+template <class SI, class SO, class SL>
 __global__ void __launch_bounds__(256) k_layer(const Geom g, const SiteMap sm, const typename SL::P* __restrict__ U,
                                                const float2* __restrict__ W, const typename SI::P* __restrict__ Zin,
-                                               typename SO::P* __restrict__ Zout, const int c0, const int ntile) {
+                                               typename SO::P* __restrict__ Zout) {
     using R = typename SL::R;
     const size_t V = g.V;
     const int s = map_site(g, sm, blockIdx.x, threadIdx.x);
-    const int tile = blockIdx.y * blockDim.y + threadIdx.y;
-    if (s < 0 || tile >= ntile) return;
+    if (s < 0) return;
     const int co[4] = {s % g.lx, (s / g.lx) % g.ly, (s / g.sxy) % g.lz, s / g.sxyz};
     const int ext[4] = {g.lx, g.ly, g.lz, g.lt};
     const int str[4] = {1, g.lx, g.sxy, g.sxyz};
-    const size_t col0 = (size_t)(c0 + tile * CT);
+    const size_t col = threadIdx.y;
     auto fwd_site = [&](int mu) {
         return (co[mu] + 1 == ext[mu]) ? s - (ext[mu] - 1) * str[mu] : s + str[mu];
     };
     auto bwd_site = [&](int mu) { return (co[mu] == 0) ? s + (ext[mu] - 1) * str[mu] : s - str[mu]; };
     const size_t KS = vec_plane(g);
     const auto vo = [&](int n) { return vec_site(g, n); };
-    cx<R> acc[CT][12];
+    const typename SI::P* zc = Zin + col * 12 * V;
+    cx<R> acc[12];
 #pragma unroll
-    for (int c = 0; c < CT; ++c)
-#pragma unroll
-        for (int k = 0; k < 12; ++k) acc[c][k] = {R(0), R(0)};
+    for (int k = 0; k < 12; ++k) acc[k] = {R(0), R(0)};
     // one operand set (two would halve the occupancy)
-    Term<R, CT> A;
-    term_load<0, SI, SL>(A, U, 0, s, Zin, V, KS, col0, vo(s));
+    Term<R> A;
+    term_load<0, SI, SL>(A, U, 0, s, zc, V, KS, vo(s));
     term_apply<0>(A, W, acc);
 #pragma unroll 1
     for (int mu = 0; mu < 4; ++mu) {
-        term_load<1, SI, SL>(A, U, mu, s, Zin, V, KS, col0, vo(fwd_site(mu)));
+        term_load<1, SI, SL>(A, U, mu, s, zc, V, KS, vo(fwd_site(mu)));
         term_apply<1>(A, W + (1 + 2 * mu) * 16, acc);
         const int bw = bwd_site(mu);
-        term_load<2, SI, SL>(A, U, mu, bw, Zin, V, KS, col0, vo(bw));
+        term_load<2, SI, SL>(A, U, mu, bw, zc, V, KS, vo(bw));
         term_apply<2>(A, W + (2 + 2 * mu) * 16, acc);
     }
+    typename SO::P* oc = Zout + col * 12 * V;
 #pragma unroll
-    for (int c = 0; c < CT; ++c) {
-        typename SO::P* oc = Zout + (col0 + c) * 12 * V;
-#pragma unroll
-        for (int k = 0; k < 12; ++k)
-            SO::st(oc, (size_t)k * KS + vo(s),
-                   cx<typename SO::R>{(typename SO::R)acc[c][k].re, (typename SO::R)acc[c][k].im});
-    }
+    for (int k = 0; k < 12; ++k)
+        SO::st(oc, (size_t)k * KS + vo(s), cx<typename SO::R>{(typename SO::R)acc[k].re, (typename SO::R)acc[k].im});
 }
 
 // Adjoint weights: W'_0 = W_0^dag, W'_{+mu} = W_{-mu}^dag, W'_{-mu} = W_{+mu}^dag
@@ -450,15 +433,15 @@ __global__ void __launch_bounds__(256) k_layer_lds(const Geom g, const SiteMap s
         asm volatile("" : "+v"(ln));
         const typename SI::P* zc = Zin + (size_t)c * 12 * V;
         const size_t KS = vec_plane(g);
-        cx<R> acc[1][12];
+        cx<R> acc[12];
 #pragma unroll
-        for (int k = 0; k < 12; ++k) acc[0][k] = {R(0), R(0)};
-        Term<R, 1> t[2];
-        auto load_in = [&](Term<R, 1>& dst, int site) {
+        for (int k = 0; k < 12; ++k) acc[k] = {R(0), R(0)};
+        Term<R> t[2];
+        auto load_in = [&](Term<R>& dst, int site) {
 #pragma unroll
             for (int k = 0; k < 12; ++k) {
                 const auto v = SI::ld(zc, (size_t)k * KS + vec_site(g, site));
-                dst.p[0][k] = {(R)v.re, (R)v.im};
+                dst.p[k] = {(R)v.re, (R)v.im};
             }
         };
         load_in(t[0], nb[0]);
@@ -466,7 +449,7 @@ __global__ void __launch_bounds__(256) k_layer_lds(const Geom g, const SiteMap s
             constexpr int D = decltype(dc)::value;
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (D + 1 < 9) load_in(t[(D + 1) % 2], nb[D + 1]);
-            Term<R, 1>& cur = t[D % 2];
+            Term<R>& cur = t[D % 2];
             if constexpr (D == 0) {
                 term_apply<0>(cur, W, acc);
             } else {
@@ -486,7 +469,7 @@ __global__ void __launch_bounds__(256) k_layer_lds(const Geom g, const SiteMap s
 #pragma unroll
         for (int k = 0; k < 12; ++k)
             SO::st(oc, (size_t)k * KS + vec_site(g, s),
-                   cx<typename SO::R>{(typename SO::R)acc[0][k].re, (typename SO::R)acc[0][k].im});
+                   cx<typename SO::R>{(typename SO::R)acc[k].re, (typename SO::R)acc[k].im});
     }
 }
 
@@ -536,9 +519,9 @@ __global__ void __launch_bounds__(256) k_layer_f32(const Geom g, const SiteMap s
         int ln = lane;
         asm volatile("" : "+v"(ln));
         const typename SI::P* zc = Zin + (size_t)c * Vec<SI>::col(g);
-        cx<float> acc[1][12];
+        cx<float> acc[12];
 #pragma unroll
-        for (int k = 0; k < 12; ++k) acc[0][k] = {0.f, 0.f};
+        for (int k = 0; k < 12; ++k) acc[k] = {0.f, 0.f};
         // the next term's spinor (and link) in flight during the current term; an FP64 input is
         // rounded where it is used, so that the rounding does not wait for the load
         cx<typename SI::R> raw[2][12];
@@ -561,9 +544,9 @@ __global__ void __launch_bounds__(256) k_layer_f32(const Geom g, const SiteMap s
             constexpr int D = decltype(dc)::value;
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (D + 1 < kND) load_in(std::integral_constant<int, D + 1>{});
-            Term<float, 1> cur;
+            Term<float> cur;
 #pragma unroll
-            for (int k = 0; k < 12; ++k) cur.p[0][k] = {(float)raw[D % 2][k].re, (float)raw[D % 2][k].im};
+            for (int k = 0; k < 12; ++k) cur.p[k] = {(float)raw[D % 2][k].re, (float)raw[D % 2][k].im};
             if constexpr (D > 0) {
 #pragma unroll
                 for (int k = 0; k < 9; ++k) {
@@ -581,7 +564,7 @@ __global__ void __launch_bounds__(256) k_layer_f32(const Geom g, const SiteMap s
         typename SO::P* oc = Zout + (size_t)c * Vec<SO>::col(g);
         const uint32_t oy = Vec<SO>::off(g, s);
         const size_t KSy = Vec<SO>::plane(g);
-        Vec<SO>::template store<false>(oc, KSy, oy, acc[0]);
+        Vec<SO>::template store<false>(oc, KSy, oy, acc);
     };
     if constexpr (LU) {
         const int c1 = min(L, (int)(blockIdx.y + 1) * cpg);
@@ -611,7 +594,7 @@ hipError_t launch_layer(const wd_ctx* c, const typename SL::P* U, const float2* 
     }
     const SiteMap sm = make_site_map_rows(c->g, 12.0 * L * sizeof(typename SI::P) + 36.0 * sizeof(typename SL::P), 4);
     dim3 block(64, L), grid(sm.nblk);
-    k_layer<SI, SO, SL, 1><<<grid, block, 0, s>>>(c->g, sm, U, W, (const typename SI::P*)in, (typename SO::P*)out, 0, L);
+    k_layer<SI, SO, SL><<<grid, block, 0, s>>>(c->g, sm, U, W, (const typename SI::P*)in, (typename SO::P*)out);
     return hipGetLastError();
 }
 

@@ -246,9 +246,11 @@ __global__ void k_convert(const double2* __restrict__ src, typename S::P* __rest
 }
 
 // FP64 block vector (layout of g) -> library block in storage S: a thread takes the G planes of one
-// 16-byte word, so that a wavefront reads runs of 64 pairs and writes 1 KB (one plane per thread
-// left 4- or 8-byte pieces of every word to separate wavefronts: A X in BF16 at 24^3 x 48, standard
-// layout, took 721 us at L = 8 and 1359 at L = 16; 619 and 1163 now).  Column blockIdx.y.
+// 16-byte word, so that a wavefront reads runs of 64 pairs and writes 1 KB.  One plane per thread
+// left 4- or 8-byte pieces of every word to separate wavefronts: BF16 at 32^3 x 64, L = 12, 1688 us in
+// the standard layout and 951 in the tiled one; 1057 and 970 now (FP32 1910 and 1160; 1227 and 1132).
+// The source is read once and streamed past the blocks that the next kernel reads (without that
+// 1178 and 1033 us).  Column blockIdx.y.
 template <class S>
 __global__ void __launch_bounds__(256)
     k_to_lowp(const double2* __restrict__ src, typename S::P* __restrict__ dst, const Geom g, uint32_t words) {
@@ -263,7 +265,7 @@ __global__ void __launch_bounds__(256)
     const double2* p = src + col * 12 * g.V + vec_site(g, s) + k * vec_plane(g);
     cx<double> v[G];
 #pragma unroll
-    for (int q = 0; q < G; ++q) v[q] = StF64::ld(p, q * vec_plane(g));
+    for (int q = 0; q < G; ++q) v[q] = StF64::ld_nt(p + q * vec_plane(g));
     V::template store_group<false>(dst + col * V::col(g), k, V::off(g, s), v);
 }
 

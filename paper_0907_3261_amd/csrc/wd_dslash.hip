@@ -352,15 +352,25 @@ __global__ void __launch_bounds__(256)
                                 if (j != i) q = q - T.at(i, j) * xs[j];
                             r = T.d[i] * q;
                         }
-                        out[i] = r;
+                        // FP64 elements are stored as they are done, library blocks by whole words
+                        // below (four FP64 sweeps of one column at 8^3 x 16: 41.7 us with all stores
+                        // at the end, 41.1 so; 12^3 x 24: 78.4 and 77.2)
+                        if constexpr (Vec<SY>::G == 1)
+                            store_out<SY>(Yc + (size_t)c * csy + (size_t)(6 * chir + i) * KSy, o_y, r);
+                        else
+                            out[i] = r;
                     }
+                    if constexpr (Vec<SY>::G > 1) {
 #pragma unroll
-                    for (int i = 0; i < 6; ++i) acc[c][6 * chir + i] = out[i];
+                        for (int i = 0; i < 6; ++i) acc[c][6 * chir + i] = out[i];
+                    }
                 }
             }
         }
+        if constexpr (Vec<SY>::G > 1) {
 #pragma unroll
-        for (int c = 0; c < CT; ++c) Vec<SY>::template store<true>(Yc + (size_t)c * csy, KSy, o_y, acc[c]);
+            for (int c = 0; c < CT; ++c) Vec<SY>::template store<true>(Yc + (size_t)c * csy, KSy, o_y, acc[c]);
+        }
     }
 }
 

@@ -220,10 +220,12 @@ __global__ void __launch_bounds__(kWG) k_reduce_rows(const double2* __restrict__
     }
 }
 
-// Threads per entry for E = L * L + extras entries: 1024 threads shared by the entries, the split
-// (and with it the order of the sums) of a reduction in one workgroup.  Close to the critical
-// kappa the last bit of the sums moves the iteration count: 32^3 x 64, L = 12, kappa = 0.127 takes
-// 61 iterations with this order and 66 with sixteen threads for every L.
+// Threads per entry for E = L * L + extras entries: 1024 threads shared by the entries, at most
+// sixteen.  For the tiles of L >= 8 this is the split (and with it the order of the sums) of a
+// reduction in one workgroup of 1024 threads; for narrower tiles and for column norms that one had
+// more threads per entry and another order.  Close to the critical kappa the last bit of the sums moves
+// the iteration count: 32^3 x 64, L = 12, kappa = 0.127 takes 61 iterations with this order and 66
+// with sixteen threads for every L.
 inline int reduce_groups(int E) {
     const int g = 1024 / E;
     return g < 16 ? g : 16;
@@ -242,8 +244,9 @@ __device__ __forceinline__ cx<double> lane_of(cx<double> v, int l) { return {lan
 
 // Solve M Z = RHS (L <= LM) by LU with partial pivoting in one wavefront: lane c < L holds column
 // c of M in a[0 .. L), lane L + c column c of RHS, and returns column c of Z in x.  Everything
-// stays in registers, the pivot column and the factors reach the other lanes by lane reads; the
-// solve in LDS by 1024 threads spent its 30 us in barriers and one thread's searches.
+// stays in registers, the pivot column and the factors reach the other lanes by lane reads, without
+// a barrier or another thread's search to wait for.  k_solve_alpha and k_solve_gamma still take 25
+// and 30 us at L = 12: one wave's serial chain of unrolled code.
 // False (in every lane) on a pivot below 1e-14 max|M| or a non-finite entry.  pmax / pmin of
 // the pivot moduli is a cheap estimate of the condition of M (a lower bound of it for this
 // pivot order).
@@ -613,8 +616,6 @@ __global__ void __launch_bounds__(kWG) k_update_U(const double2* __restrict__ P,
     }
 }
 
-// X += zeta F + G ; R <- R - zeta W - Y ; per-column ||R||^2 into the partial
-// extras (one thread per row, L columns; coalesced across the wavefront).
 // R = B - AX elementwise; R may be AX (each element is read before it is written)
 __global__ void k_axpby(const double2* __restrict__ B, const double2* AX, double2* R, size_t n) {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;

@@ -454,7 +454,8 @@ inline SiteMap make_site_map_rows(const Geom& g, double bytes_site, int tb = 1) 
 // takes all columns of its tile, so that the links and blocks are staged once, unless the tiles
 // alone leave CUs empty: then groups of four columns and more, as many as fit the chip at once
 // (FP64 sweep at 8^3 x 16, L = 12, 128 tiles: 22.2 us in two groups against 25.7 in one;
-// BF16 sweeps there 13.0 against 27).
+// BF16 sweeps there 13.0 against 27).  nblk is the size of the grid: where the XCDs' shares of the
+// lattice are uneven it counts workgroups without a site too, and the groups are fewer than would fit.
 inline int cols_per_group(int nblk, int L, int per_cu) {
     const int room = 256 * per_cu / nblk, most = (L + 3) / 4;
     const int groups = room < 1 ? 1 : (room < most ? room : most);

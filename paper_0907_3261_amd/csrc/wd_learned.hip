@@ -142,11 +142,14 @@ constexpr int kGB = 256;  // threads of the reduction kernels
 // the colour sums in FP32, the site sums in FP64.  A workgroup takes (tile, column) pairs of 64
 // sites in turn; its wave d - 1 forms the columns t = 2 h and 2 h + 1 (h = blockIdx.y) of hop
 // direction d, and one of the sixteen elements of the self term, so that no wave keeps more than
-// nine complex sums and six waves fit a SIMD.  The gradient's spinor and the neighbours' come from
+// nine complex sums.  The gradient's spinor and the neighbours' come from
 // memory once and from the caches after that; a launch per direction read both again for each.
-// What bounds it now is the L1: 30 loads a wave and pair, of which the 18 of the link are 256 B
-// each.  16^3 x 32, L = 12, one layer with its reductions: 9 x (60 + 13) us by direction, 391 us
-// (FP64 input 525).
+// What bounds it now is the L1: 33 loads a wave and pair (36 from FP64 activations), of which the 18
+// of the link are 256 B each.  16^3 x 32, L = 12, one layer with its reductions: 9 x (60 + 13) us by
+// direction, 391 us (FP64 input 525).
+// The grid gives a SIMD four waves; the bound is set for six because the code for the 80 registers
+// that it leaves is the faster one, though the FP32 instance spills one (whole gradient call at
+// 16^3 x 32, L = 12: 2206 us, 2342 with the bound at four; 24^3 x 48: 11.8 and 12.9 ms).
 constexpr int kWgBlocks = 256;  // workgroups per h
 template <class SZ>
 __global__ void __launch_bounds__(512, 6) k_wgrad(const Geom g, const float* __restrict__ U,

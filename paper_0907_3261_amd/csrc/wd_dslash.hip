@@ -924,8 +924,8 @@ hipError_t launch_hop_ct(const Geom& g, const LinkInfo& li, const void* Uk, cons
     const SiteMap sm =
         make_site_map(g, 12.0 * CT * ntiles * sizeof(typename SF::P) + 72.0 * sizeof(typename SC::P));
     // one FP32 column: eight waves to a CU, held there by LDS that nothing uses; more of them push
-    // each other's neighbours out of the L2.  A sweep at 32^3 x 64 reads 1.22 GB from memory with the
-    // twenty that the registers allow, 0.90 with eight; four sweeps there 1366 us with twenty,
+    // each other's neighbours out of the L2.  A sweep at 32^3 x 64 fetches 2.50 GB with the
+    // twenty that the registers allow, 1.84 with eight; four sweeps there 1366 us with twenty,
     // 1312, 1284 and 1260 with sixteen, twelve and eight (24^3 x 48: 437, 430, 408 and 406;
     // 16^3 x 32: 93 with any)
     const unsigned spare = Vec<SF>::G == 2 && CT == 1 && ntiles == 1 ? 160 * 1024 / 8 : 0;

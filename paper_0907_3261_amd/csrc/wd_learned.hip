@@ -614,7 +614,7 @@ hipError_t launch_layer(const wd_ctx* c, const float2* W, const void* in, void* 
     } else {
         // one column from FP64: eight waves to a CU, held there by LDS that nothing uses.  With the
         // twelve that the registers allow, the neighbours' spinors (12 KB a wave and term) push
-        // each other out of the L2: 1.62 GB read from memory at 32^3 x 64, 1.08 with eight (learned
+        // each other out of the L2: 3.31 GB fetched at 32^3 x 64, 2.22 with eight (learned
         // M there 1068 and 968 us; 20^3 x 40: 197 and 182; 16^3 x 32 and smaller the same)
         const unsigned spare = std::is_same_v<SI, StF64> && L == 1 ? 160 * 1024 / 8 : 0;
         k_layer_f32<SI, SO, false><<<sm.nblk, dim3(64, L), spare, s>>>(c->g, sm, c->U32, W, zi, zo, L, L);

@@ -248,10 +248,9 @@ __global__ void k_convert(const double2* __restrict__ src, typename S::P* __rest
 // FP64 block vector (layout of g) -> library block in storage S: a thread takes the G planes of one
 // 16-byte word, so that a wavefront reads runs of 64 pairs and writes 1 KB.  One plane per thread
 // left 4- or 8-byte pieces of every word to separate wavefronts: BF16 at 32^3 x 64, L = 12, 1688 us in
-// the standard layout and 951 in the tiled one; 1057 and 970 now (FP32 1910 and 1160; 1227 and 1132).
-// The source is read once and streamed past the blocks that the next kernel reads (without that
-// 1178 and 1033 us).  Column blockIdx.y.
-template <class S>
+// the standard layout and 951 in the tiled one; 1056 and 969 now (FP32 1910 and 1160; 1195 and 1118).
+// Column blockIdx.y.  NT: streaming loads and stores.
+template <class S, bool NT>
 __global__ void __launch_bounds__(256)
     k_to_lowp(const double2* __restrict__ src, typename S::P* __restrict__ dst, const Geom g, uint32_t words) {
     using V = Vec<S>;
@@ -265,8 +264,8 @@ __global__ void __launch_bounds__(256)
     const double2* p = src + col * 12 * g.V + vec_site(g, s) + k * vec_plane(g);
     cx<double> v[G];
 #pragma unroll
-    for (int q = 0; q < G; ++q) v[q] = StF64::ld_nt(p + q * vec_plane(g));
-    V::template store_group<false>(dst + col * V::col(g), k, V::off(g, s), v);
+    for (int q = 0; q < G; ++q) v[q] = NT ? StF64::ld_nt(p + q * vec_plane(g)) : StF64::ld(p, q * vec_plane(g));
+    V::template store_group<NT>(dst + col * V::col(g), k, V::off(g, s), v);
 }
 
 __global__ void k_links_f32(const double2* __restrict__ src, float* __restrict__ dst, size_t V) {
@@ -323,17 +322,28 @@ hipError_t launch_point_form(const double2* T, double2* Tp, size_t V, hipStream_
     return hipGetLastError();
 }
 
+template <class S>
+static void to_lowp(const double2* src, void* dst, const Geom& g, int L, hipStream_t s) {
+    using P = typename S::P;
+    const uint32_t words = (uint32_t)lowp_tiles(g) * 64 * (12 / Vec<S>::G);
+    const dim3 grid(nblk(words, 256), L);
+    // streamed where source and words together exceed the 256 MB Infinity Cache, else left there for
+    // the operator behind it (tiled A X with plain / streaming accesses, us: BF16 24^3 x 48, L = 4, 612 MB,
+    // 333 / 314; 20^3 x 40, L = 4, 307 MB, 184 / 174 and L = 3, 230 MB, 147 / 151; 12^3 x 24, L = 12, 119 MB,
+    // 72 / 81; FP32 20^3 x 40, L = 3, 276 MB, 189 / 164; 16^3 x 32, L = 4, 151 MB, 76 / 87)
+    if ((double)g.V * L * 12.0 * (16 + sizeof(P)) > 256.0 * 1024 * 1024)
+        k_to_lowp<S, true><<<grid, 256, 0, s>>>(src, (P*)dst, g, words);
+    else
+        k_to_lowp<S, false><<<grid, 256, 0, s>>>(src, (P*)dst, g, words);
+}
+
 hipError_t launch_to_lowp(const double2* src, void* dst, Prec p, const Geom& g, int L, hipStream_t s) {
-    const uint32_t sites = (uint32_t)lowp_tiles(g) * 64;
-    if (p == Prec::F32) {
-        const uint32_t words = sites * (12 / Vec<StF32P>::G);
-        k_to_lowp<StF32P><<<dim3(nblk(words, 256), L), 256, 0, s>>>(src, (float2*)dst, g, words);
-    } else if (p == Prec::BF16) {
-        const uint32_t words = sites * (12 / Vec<StBF16>::G);
-        k_to_lowp<StBF16><<<dim3(nblk(words, 256), L), 256, 0, s>>>(src, (uint32_t*)dst, g, words);
-    } else {
+    if (p == Prec::F32)
+        to_lowp<StF32P>(src, dst, g, L, s);
+    else if (p == Prec::BF16)
+        to_lowp<StBF16>(src, dst, g, L, s);
+    else
         return hipErrorInvalidValue;
-    }
     return hipGetLastError();
 }
 

@@ -80,3 +80,18 @@ def test_bf16_pairs(pkg, L):
     Zo = op.to_block(jacobi_sweeps_lowp(op, op.from_block(R), 3, "bf16"))
     assert _maxrel(Z, Zo) < 2.0 ** -7 and np.linalg.norm(Z - Zo) < 1e-3 * np.linalg.norm(Zo)
     c.close()
+
+
+# the conversion of a block streams where block and copy exceed 256 MB: sixteen columns of these
+# lattices do, four do not.  A column's value does not depend on the width of its block
+@pytest.mark.parametrize("prec", ["f32", "bf16"])
+@pytest.mark.parametrize("dims,layout", [((21, 17, 16, 13), "standard"), ((16, 16, 16, 20), "tiled")])
+def test_apply_on_streamed_blocks(pkg, dims, layout, prec):
+    c, op, _ = _ctx(pkg, dims, 16, 328)
+    c.set_layout(layout)
+    R = torch.from_numpy(wi.gaussian_block(op.V, 16, 329)).cuda()
+    Y = c.apply(R, prec=prec)
+    assert torch.isfinite(torch.view_as_real(Y)).all()
+    for lo in (0, 7, 12):
+        assert torch.equal(c.apply(R[lo:lo + 4].contiguous(), prec=prec), Y[lo:lo + 4])
+    c.close()

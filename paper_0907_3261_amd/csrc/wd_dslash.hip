@@ -353,8 +353,8 @@ __global__ void __launch_bounds__(256)
                             r = T.d[i] * q;
                         }
                         // FP64 elements are stored as they are done, library blocks by whole words
-                        // below (four FP64 sweeps of one column at 8^3 x 16: 41.7 us with all stores
-                        // at the end, 41.1 so; 12^3 x 24: 78.4 and 77.2)
+                        // below (four FP64 sweeps with all stores at the end and so: 8^3 x 16, L = 1, 41.7
+                        // and 41.1 us; point reading, 20^3 x 40, L = 2, 786 and 731, L = 1, 520 and 488)
                         if constexpr (Vec<SY>::G == 1)
                             store_out<SY>(Yc + (size_t)c * csy + (size_t)(6 * chir + i) * KSy, o_y, r);
                         else
